@@ -11,11 +11,12 @@
 //                     x 256 tiles on 16 waves (128 x 128 on 4 for small
 //                     problems); dense, split-K, routed experts and the fused
 //                     epilogues (SwiGLU forward/backward, factor gradients).
-//                     It serves every projection of the calibration step.
+//                     It serves every projection of the calibration step, and
+//                     ragged extents in every direction.
 //   gemm_bf16_kernel  register-staged tiles, operands contiguous along the
 //                     output dimension transposed in registers with v_perm;
-//                     the remaining shapes (unaligned extents, batched
-//                     attention products of the unfused path).
+//                     the batched attention products of the unfused path, and
+//                     row pitches or K-major operands beyond 32-bit offsets.
 // Both map workgroups to tiles so that neighbouring tiles share an XCD's L2
 // (workgroups are dealt round-robin to the 8 XCDs).
 #include <cmath>
@@ -398,7 +399,8 @@ __device__ __forceinline__ void store4f(bf16* p, f32x4 v) {
 //   c0..c0+15, lane i gets column c0+i at rows k0..k0+3: the MFMA operand
 //   (one column, consecutive k) without any transpose pass.  The XOR puts the
 //   4 rows x 64 B that 32 lanes read in one cycle on 4 different 64-byte bank
-//   windows.  COLS must divide the matrix extent.
+//   windows.  Columns past the matrix extent (a multiple of 8) hold the next
+//   row's values or zero; their results are never stored.
 //
 // The swizzles are chosen through the global address each lane fetches.  Two
 // LDS stages: the next tile is fetched while the current one is multiplied.
@@ -410,8 +412,11 @@ __device__ __forceinline__ void store4f(bf16* p, f32x4 v) {
 // K-contiguous operand tile, ROWS x 64, for NW waves.  Buffer loads from the
 // tile's first row: instructions i and i+2 differ only by 16 rows (a uniform
 // offset), so a lane keeps two 32-bit offsets; rows past the matrix read as
-// zero (their results are never stored).
-template <int ROWS, int NW>
+// zero (their results are never stored).  KR (a contraction extent that is a
+// multiple of 8 but not of 64): a lane whose 16-byte chunk lies past the
+// extent reads past the resource's end, so as zero, and not the next row's
+// first values (a NaN there must not reach this row).
+template <int ROWS, int NW, bool KR>
 struct DmaOpNT {
   static constexpr int NI = ROWS / 8 / NW;  // 1 KB instructions per wave
   static constexpr int READS = 1;           // LDS reads per fragment
@@ -420,6 +425,8 @@ struct DmaOpNT {
   uint64_t bytes;        // bytes from panel to the end of the matrix
   uint32_t step;         // bytes between instructions i and i+2 (uniform)
   uint32_t voff[2];      // per lane, instructions of parity 0 and 1
+  int kc[KR ? 2 : 1];    // KR: first k of the lane's chunk within a k tile
+  int64_t k_end;         // KR: end of the contraction range
   i32x4_rsrc rs;         // the tile's rows from the first k of its range
   int64_t k_first;
   __device__ __forceinline__ void init(const bf16* base, int64_t ld, int64_t row0, int64_t rows,
@@ -433,6 +440,7 @@ struct DmaOpNT {
       const int blk = wave * NI + p;
       const int c = (lane & 7) ^ (((blk & 1) << 2) | (rl >> 1));
       voff[p] = (uint32_t)((blk * 8 + rl) * ld * 2 + c * 16);
+      if constexpr (KR) kc[p] = 8 * c;
     }
   }
   // tile row r holds matrix row half*(r & 1) + (row0 + r)/2 (row0 even):
@@ -455,17 +463,26 @@ struct DmaOpNT {
   }
   // one resource per tile, from the first k of the tile's contraction range
   // (the k offset of each copy goes in its scalar offset)
-  __device__ __forceinline__ void bind(int64_t kb, int64_t) {
+  __device__ __forceinline__ void bind(int64_t kb, int64_t ke) {
     const uint64_t b = (uint64_t)kb * 2;
-    rs = buf_rsrc(panel + b, (uint32_t)min(bytes - b, (uint64_t)0xFFFFFFFFu));
+    // (KR: a tile spans at most 2^31 bytes, so kPast below lies past any size)
+    rs = buf_rsrc(panel + b, (uint32_t)min(bytes - b, (uint64_t)(KR ? 0x80000000u : 0xFFFFFFFFu)));
     k_first = kb;
+    k_end = ke;
   }
-  // (K-contiguous rows are whole: the contraction extent is a multiple of 64)
+  // (without KR the rows are whole: the contraction extent is a multiple of 64)
   __device__ __forceinline__ void issue(uint32_t lds, int64_t k0, int wave) const {
     const uint32_t ko = (uint32_t)(k0 - k_first) * 2;
+    uint32_t vo[2] = {voff[0], voff[1]};
+    if constexpr (KR) {
+      constexpr uint32_t kPast = 0xF0000000u;
+      const int lim = (int)min<int64_t>(k_end - k0, 64);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) vo[p] = kc[p] < lim ? vo[p] : kPast;
+    }
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-      dma16_lds(rs, voff[i & 1], ko + (uint32_t)(i >> 1) * step, lds + (wave * NI + i) * 1024);
+      dma16_lds(rs, vo[i & 1], ko + (uint32_t)(i >> 1) * step, lds + (wave * NI + i) * 1024);
   }
   // rows row0 .. row0+31 (lane: row row0 + lane%32), k = 16 kk + 8 (lane/32) .. +7
   __device__ __forceinline__ bf16x8 frag(const uint4* lds, int row0, int kk, int lane) const {
@@ -487,13 +504,15 @@ struct DmaOpKM {
   static_assert(NI >= 1 && RPI >= 1 && NI % P == 0, "tile too small for the wave count");
   const char* panel;     // byte address of the tile's first column, row 0 (uniform)
   uint32_t ld2;          // row pitch in bytes
+  uint32_t tail;         // bytes of a row from the tile's first column to the extent
   uint32_t voff[P];      // per lane
-  i32x4_rsrc rs;         // rows kb .. ke - 1 of the tile's columns
+  i32x4_rsrc rs;         // rows kb .. ke - 1 from the tile's first column
   int64_t k_first;
-  __device__ __forceinline__ void init(const bf16* base, int64_t ld, int64_t col0, int64_t,
+  __device__ __forceinline__ void init(const bf16* base, int64_t ld, int64_t col0, int64_t cols,
                                        int wave, int lane) {
     panel = reinterpret_cast<const char*>(base + col0);
     ld2 = (uint32_t)(ld * 2);
+    tail = (uint32_t)((cols - col0) * 2);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int row = (wave * NI + p) * RPI + lane / CPR;
@@ -501,10 +520,12 @@ struct DmaOpKM {
       voff[p] = (uint32_t)(row * ld * 2 + c * 16);
     }
   }
-  // one resource per tile over rows kb .. ke - 1 (rows at or past ke read as
-  // zero; the host keeps (ke - kb + 64) * ld2 below 2^32)
+  // one resource per tile over rows kb .. ke - 1, ending at the extent's end
+  // of row ke - 1 (rows at or past ke read as zero; the host keeps
+  // (ke - kb + 64) * ld2 below 2^32)
   __device__ __forceinline__ void bind(int64_t kb, int64_t ke) {
-    rs = buf_rsrc(panel + (uint64_t)kb * ld2, (uint32_t)((uint64_t)(ke - kb) * ld2));
+    rs = buf_rsrc(panel + (uint64_t)kb * ld2,
+                  ke > kb ? (uint32_t)((uint64_t)(ke - kb - 1) * ld2) + tail : 0u);
     k_first = kb;
   }
   // rows k0 .. k0 + 63 of the range
@@ -567,7 +588,7 @@ __device__ __forceinline__ bool group_tile(const int64_t* off, int E, int t, int
 }
 
 template <int BM, int BN, int WGM, int WGN, bool AKM, bool BKM, typename OutT, typename RT,
-          bool HAS_R, int EPI = 0, int SB = 2>
+          bool HAS_R, int EPI = 0, int SB = 2, bool KR = false>
 __global__ __launch_bounds__(WGM* WGN * 64, 1)
     __attribute__((amdgpu_waves_per_eu(1, (WGM * WGN + 3) / 4))) void gemm_dma_kernel(GemmLaunch L) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -575,8 +596,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int FM = WTM / 32, FN = WTN / 32;
   static_assert(FM >= 1 && FN >= 1 && FM * FN >= FM + FN, "bad tile");
-  using OA = std::conditional_t<AKM, DmaOpKM<BM, NW>, DmaOpNT<BM, NW>>;
-  using OB = std::conditional_t<BKM, DmaOpKM<BN, NW>, DmaOpNT<BN, NW>>;
+  using OA = std::conditional_t<AKM, DmaOpKM<BM, NW>, DmaOpNT<BM, NW, KR>>;
+  using OB = std::conditional_t<BKM, DmaOpKM<BN, NW>, DmaOpNT<BN, NW, KR>>;
   // one LDS allocation: the two stages of A, then the SB of B (the epilogue
   // stages the output through the first two stages' worth of it).  SB = 3
   // puts B's copies two k tiles ahead, for B streamed from HBM once (a large
@@ -726,8 +747,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
       constexpr int HP3 = 2, SR3 = 16;
       const int64_t mrow = m0 + wm * WTM + (p / HP3) * 32 + (p % HP3) * SR3;
       const int64_t wrow = (int64_t)z * g.M + min(mrow + (lane >> 2), m_lim - 1);
-      const bf16* wsrc = reinterpret_cast<const bf16*>(g.fac.W) + wrow * g.fac.ldw + n0 +
-                         wn * WTN + (lane & 3) * 16;
+      const bf16* wsrc = reinterpret_cast<const bf16*>(g.fac.W) + wrow * g.fac.ldw +
+                         min(n0 + wn * WTN + (lane & 3) * 16, g.N - 16);
 #pragma unroll
       for (int q = 0; q < 4; ++q) epw[q] = raw4(wsrc + 4 * q);
     }
@@ -817,7 +838,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
       static_assert(BM * GPT <= NW * 64, "one reduced group per thread");
       const FacEpi& F = g.fac;
       const int rr = lane >> 2, cq = (lane & 3) * 16;
-      const int64_t ncol = n0 + wn * WTN + cq;
+      // rows past M and columns past N (a multiple of 128) are clamped into
+      // the matrix for every load; their groups are not written
+      const int64_t ncol = min(n0 + wn * WTN + cq, g.N - 16);
       // The raw group scalars (mu0, alpha0 and the three factors) of a part's
       // row, loaded one part ahead, and those of the group this thread
       // reduces at the end, loaded with the last part: with a few k tiles
@@ -835,7 +858,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
         return ((int64_t)z * g.M + min(mrow + rr, m_lim - 1)) * (F.ldw >> 7) + (ncol >> 7);
       };
       const int ft = min(tid, BM * GPT - 1), frow = ft / GPT, fgt = ft % GPT;
-      const int64_t fgrp = ((int64_t)z * g.M + m0 + frow) * (F.ldw >> 7) + (n0 >> 7) + fgt;
+      const int64_t fgrp = ((int64_t)z * g.M + min(m0 + frow, m_lim - 1)) * (F.ldw >> 7) +
+                           min((n0 >> 7) + fgt, (g.N >> 7) - 1);
       float gsf[5], gsc[5], gsn[5];
       raw_scalars(part_group(0), gsc);
 #pragma unroll
@@ -950,7 +974,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
       // both halves of each group in order, then the three factor gradients
       // (the separate factor-gradient kernel's formulas)
       __syncthreads();
-      if (tid < BM * GPT) {
+      if (tid < BM * GPT && m0 + frow < m_lim && n0 + 128 * fgt < g.N) {
         const int row = frow, gt = fgt;
         const float* a0 = fsum + (row * WGN + 2 * gt) * 4;
         // the constant factors of f (k2, soft only), f_W and f_Delta (sk4)
@@ -1169,9 +1193,14 @@ static void launch_cfg(GemmLaunch& L, hipStream_t stream) {
 }
 
 template <int BM, int BN, int WGM, int WGN, bool AKM, bool BKM, typename OutT, typename RT,
-          int EPI = 0, int SB = 2>
+          int EPI = 0, int SB = 2, bool KR = false>
 static void launch_dma(GemmLaunch& L, hipStream_t stream) {
   const GemmArgs& g = L.g;
+  // a K-contiguous operand whose contraction extent is not whole 64-deep
+  // tiles takes the variant that bounds each row (KR)
+  if constexpr (!KR && EPI == 0 && !(AKM && BKM)) {
+    if (g.K % 64 != 0) return launch_dma<BM, BN, WGM, WGN, AKM, BKM, OutT, RT, EPI, SB, true>(L, stream);
+  }
   // Bands of the tile walk: 8 tile rows (of the 32 tiles in flight per XCD,
   // 8 x 4), but 2 (2 x 16) for the weight-gradient products, both operands
   // K-major: measured in the 14B-shaped calibration step, their launches
@@ -1184,11 +1213,12 @@ static void launch_dma(GemmLaunch& L, hipStream_t stream) {
   dim3 grid((unsigned)(L.tiles_m * L.tiles_n * (g.group_mode == 2 ? g.n_groups : L.ksplit)));
   dim3 block(WGM * WGN * 64);
   char tag[112];
-  std::snprintf(tag, sizeof(tag), "gemm_dma_kernel<%d, %d, %d, %d, %s%s, %s, %s, %s%s%s%s>", BM,
+  std::snprintf(tag, sizeof(tag), "gemm_dma_kernel<%d, %d, %d, %d, %s%s, %s, %s, %s%s%s%s%s>", BM,
                 BN, WGM, WGN, AKM ? "k" : "n", BKM ? "k" : "t", tname<OutT>(), tname<RT>(),
                 g.R ? "true" : "false",
                 EPI == 1 ? ", swiglu" : (EPI == 2 ? ", swiglu_bwd" : (EPI == 3 ? ", factor_grads" : "")),
-                g.group_mode ? ", experts" : "", SB == 3 ? ", 3 B stages" : "");
+                g.group_mode ? ", experts" : "", SB == 3 ? ", 3 B stages" : "",
+                KR ? ", ragged k" : "");
   double flops, bytes;
   gemm_work(L, (int)sizeof(OutT), flops, bytes);
   if (EPI == 1) bytes += (double)g.M * (double)(g.N / 2) * 2.0;          // a written
@@ -1199,31 +1229,31 @@ static void launch_dma(GemmLaunch& L, hipStream_t stream) {
   }
   if (g.R)
     CATQ_TRACED(stream, tag, flops, bytes, g.M, g.N, g.K,
-                hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, AKM, BKM, OutT, RT, true, EPI, SB>),
+                hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, AKM, BKM, OutT, RT, true, EPI, SB, KR>),
                                    grid, block, 0, stream, L));
   else
     CATQ_TRACED(stream, tag, flops, bytes, g.M, g.N, g.K,
-                hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, AKM, BKM, OutT, RT, false, EPI, SB>),
+                hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, AKM, BKM, OutT, RT, false, EPI, SB, KR>),
                                    grid, block, 0, stream, L));
 }
 
-// The direct-to-LDS kernel serves dense bf16 problems with K (per split) a
-// multiple of 64 and row pitches below 4M elements; a K-major operand also
-// needs its tile extent to divide the matrix extent.
-static bool dma_ok(const GemmLaunch& L, int a_t, int b_t, int bm, int bn) {
+// The direct-to-LDS kernel serves every unbatched bf16 problem whose row
+// pitches are multiples of 8 elements below 4M and whose K-major operands'
+// contraction ranges fit 32-bit offsets; extents may be ragged in every
+// direction (multiples of 8 where an operand is contiguous).
+static bool dma_ok(const GemmLaunch& L, int a_t, int b_t) {
   const GemmArgs& g = L.g;
   // grouped: rows by expert with A K-contiguous, or the contraction by
   // expert with both operands K-major (ragged groups read zero past their end)
   const bool grouping = g.group_mode == 0 || (g.group_mode == 1 && a_t == 0) ||
                         (g.group_mode == 2 && a_t == 1 && b_t == 1);
-  return grouping && g.causal == 0 && g.batch == 1 && (g.group_mode == 2 || g.K % 64 == 0) &&
+  return grouping && g.causal == 0 && g.batch == 1 && ((a_t == 1 && b_t == 1) || g.K % 8 == 0) &&
          (L.ksplit <= 1 || L.kchunk % 64 == 0) && g.lda % 8 == 0 && g.ldb % 8 == 0 &&
          g.lda < (1 << 22) && g.ldb < (1 << 22) &&  // 32-bit buffer offsets within a tile
          // a K-major operand's resource spans its whole contraction range
          (a_t == 0 || (uint64_t)(g.K + 64) * (uint64_t)g.lda * 2 < (1ull << 32)) &&
          (b_t == 0 || (uint64_t)(g.K + 64) * (uint64_t)g.ldb * 2 < (1ull << 32)) &&
-         aligned16(g.A) && aligned16(g.B) && (a_t == 0 || g.M % bm == 0) &&
-         (b_t == 0 || g.N % bn == 0);
+         aligned16(g.A) && aligned16(g.B);
 }
 
 // A dense product on 256 x 256 tiles.  An unsplit forward product (both
@@ -1239,10 +1269,15 @@ static void launch_dense256(GemmLaunch& L, hipStream_t stream) {
     launch_dma<256, 256, 4, 4, A_T == 1, B_T == 1, OutT, RT>(L, stream);
 }
 
+// The 256 x 256 tile from 160 tiles on (5/8 of the compute units busy in one
+// round still beats 128 x 128 tiles on 4 waves: the 2048 x 6144 weight
+// gradient over 8192 tokens, unsplit, takes 216 against 260 us).
+constexpr int64_t kTiles256 = 160;
+
 template <int A_T, int B_T, typename OutT, typename RT>
 static void launch_bf16(GemmLaunch& L, hipStream_t stream) {
   const GemmArgs& g = L.g;
-  if (g.group_mode == 1 && g.N >= 256 && dma_ok(L, A_T, B_T, 256, 256)) {
+  if (g.group_mode == 1 && dma_ok(L, A_T, B_T)) {
     // routed experts' rows: 256-row tiles on 16 waves, although each
     // expert's last tile is partly empty (with ~256 rows per expert, 128-row
     // tiles on 8 waves waste less but measured 25% slower).  In the forward
@@ -1256,16 +1291,13 @@ static void launch_bf16(GemmLaunch& L, hipStream_t stream) {
       launch_dma<256, 256, 4, 4, A_T == 1, B_T == 1, OutT, RT>(L, stream);
     return;
   }
-  if (g.group_mode == 2 && dma_ok(L, A_T, B_T, 256, 256)) {
+  if (g.group_mode == 2 && dma_ok(L, A_T, B_T)) {
     launch_dma<256, 256, 4, 4, A_T == 1, B_T == 1, OutT, RT>(L, stream);
     return;
   }
-  // the 256 x 256 tile from 160 tiles on (5/8 of the compute units busy in
-  // one round still beats 128 x 128 tiles on 4 waves: the 2048 x 6144 weight
-  // gradient over 8192 tokens, unsplit, takes 216 against 260 us)
   const int64_t t256 = ((g.M + 255) / 256) * ((g.N + 255) / 256) * L.ksplit;
-  if (g.group_mode == 0 && g.M >= 256 && g.N >= 256 && t256 >= 160 &&
-      dma_ok(L, A_T, B_T, 256, 256)) {
+  if (g.group_mode == 0 && g.M >= 256 && g.N >= 256 && t256 >= kTiles256 &&
+      dma_ok(L, A_T, B_T)) {
     // One workgroup of the 256 x 256 kernel fills a compute unit, so a last
     // round of a quarter to three quarters of the 256 units leaves the rest
     // idle (8192 x 5120 outputs: 640 tiles, 2.5 rounds).  Then the columns
@@ -1290,7 +1322,7 @@ static void launch_bf16(GemmLaunch& L, hipStream_t stream) {
         T.g.C = reinterpret_cast<OutT*>(g.C) + nh;
         if (g.R) T.g.R = reinterpret_cast<const RT*>(g.R) + nh;
         const int64_t t128 = ((g.M + 127) / 128) * ((T.g.N + 127) / 128);
-        if (t128 <= 512 && dma_ok(T, A_T, B_T, 128, 128)) {
+        if (t128 <= 512 && dma_ok(T, A_T, B_T)) {
           launch_dense256<A_T, B_T, OutT, RT>(H, stream);
           // the forward layout's split-off columns also take three B stages
           // (80 KB of LDS: two workgroups per unit still fit; 3-6% faster)
@@ -1305,7 +1337,7 @@ static void launch_bf16(GemmLaunch& L, hipStream_t stream) {
     launch_dense256<A_T, B_T, OutT, RT>(L, stream);
     return;
   }
-  if (g.group_mode == 0 && dma_ok(L, A_T, B_T, 128, 128)) {
+  if (g.group_mode == 0 && dma_ok(L, A_T, B_T)) {
     launch_dma<128, 128, 2, 2, A_T == 1, B_T == 1, OutT, RT>(L, stream);
     return;
   }
@@ -1392,19 +1424,19 @@ catq_status gemm_run_epi(const GemmArgs& a, int a_t, int b_t, hipStream_t stream
   // plain GEMM takes the same 256 x 256 kernel, so fused and unfused results
   // are the same bits
   const int64_t t256 = ((a.M + 255) / 256) * ((a.N + 255) / 256);
-  const bool shape = t256 >= 160 && a.R == nullptr && a.alpha == 1.0f && a.N % 4 == 0 &&
+  const bool shape = t256 >= kTiles256 && a.R == nullptr && a.alpha == 1.0f && a.N % 4 == 0 &&
                      a.ldc % 4 == 0 && a.ld_aux % 4 == 0 && aligned16(a.C) && aligned16(a.aux0) &&
                      (a.epi == 1 || aligned16(a.aux1));
   if (a.epi == 1) {
     // A [M][K] tokens (K-contiguous), B the fused weight [N][K]
-    if (!(shape && a_t == 0 && b_t == 0 && a.M >= 256 && a.N >= 256 && dma_ok(L, 0, 0, 256, 256)))
+    if (!(shape && a_t == 0 && b_t == 0 && a.M >= 256 && a.N >= 256 && a.K % 64 == 0 && dma_ok(L, 0, 0)))
       return CATQ_ERR_VALUE;
     // three B stages, as the plain forward products (bit-identical; 2.47 ->
     // 2.39 ms on the 14B-shaped gate|up in the calibration step)
     launch_dma<256, 256, 4, 4, false, false, bf16, bf16, 1, 3>(L, stream);
   } else {
     // dX-shaped: A = dY [M][K] (K-contiguous), B = W_fake [K][N] (K-major)
-    if (!(shape && a_t == 0 && b_t == 1 && a.M >= 256 && a.N >= 256 && dma_ok(L, 0, 1, 256, 256)))
+    if (!(shape && a_t == 0 && b_t == 1 && a.M >= 256 && a.N >= 256 && a.K % 64 == 0 && dma_ok(L, 0, 1)))
       return CATQ_ERR_VALUE;
     launch_dma<256, 256, 4, 4, false, true, bf16, bf16, 2>(L, stream);
   }
@@ -1423,12 +1455,12 @@ catq_status gemm_run_factor(const GemmArgs& a, hipStream_t stream) {
   L.c_split_stride = 0;
   L.tiles_m = L.tiles_n = 0;
   // G [rows][d_in] (per expert, or one dense unsplit problem) from K-major
-  // dY and X; whole 256 x 256 tiles (128-weight groups never straddle them),
-  // C only as an aligned dummy
-  const bool shape = a.M > 0 && a.N > 0 && a.M % 256 == 0 && a.N % 256 == 0 && a.alpha == 1.0f &&
+  // dY and X, d_in whole 128-weight groups (which never straddle tiles); C
+  // only as an aligned dummy
+  const bool shape = a.M > 0 && a.N > 0 && a.N % 128 == 0 && a.alpha == 1.0f &&
                      a.R == nullptr && a.c_gs == 0 && a.ldc % 4 == 0 && aligned16(a.C) &&
                      a.fac.W != nullptr && (reinterpret_cast<uintptr_t>(a.fac.W) & 7) == 0 &&
-                     a.fac.ldw == a.N && dma_ok(L, 1, 1, 256, 256);
+                     a.fac.ldw == a.N && dma_ok(L, 1, 1);
   if (!shape) return CATQ_ERR_VALUE;
   if (a.group_mode == 0) {
     // A partial last round of a quarter to three quarters of the 256
@@ -1437,8 +1469,18 @@ catq_status gemm_run_factor(const GemmArgs& a, hipStream_t stream) {
     // workgroups per unit, one round at most), with the weights, group
     // arrays and outputs taken from that column on (the row pitch of W, and
     // so the group numbering, stays the whole d_in)
-    const int tm = (int)(a.M / 256), tn = (int)(a.N / 256);
+    const int tm = (int)((a.M + 255) / 256), tn = (int)((a.N + 255) / 256);
     const int rem = (tm * tn) % 256;
+    // few tiles and a ragged token count: the product and the separate
+    // factor-gradient kernel
+    if (a.K % 64 != 0 && ((a.M + 127) / 128) * (a.N / 128) < 64) return CATQ_ERR_VALUE;
+    // fewer tiles than fill the chip: 128 x 128 (4096 x 2048 weights over 512
+    // tokens: 36 us on 128 tiles of 256 x 256, 29 us on 512 of 128 x 128)
+    if (tm * tn < kTiles256) {
+      launch_dma<128, 128, 2, 2, true, true, float, float, 3>(L, stream);
+      CATQ_CHECK_LAUNCH("gemm factor epilogue");
+      return CATQ_OK;
+    }
     int h = 0;
     if (rem >= 64 && rem <= 192)
       for (int c = tn - 1; c >= 1 && h == 0; --c)
@@ -1458,8 +1500,8 @@ catq_status gemm_run_factor(const GemmArgs& a, hipStream_t stream) {
       for (int k = 0; k < 3; ++k)
         if (F.s[k] == 1) F.out[k] += gsh;
       if (F.ws != nullptr) F.ws += gsh;
-      const int64_t t128 = (a.M / 128) * (T.g.N / 128);
-      if (t128 <= 512 && dma_ok(T, 1, 1, 128, 128)) {
+      const int64_t t128 = ((a.M + 127) / 128) * (T.g.N / 128);
+      if (t128 <= 512 && dma_ok(T, 1, 1)) {
         launch_dma<256, 256, 4, 4, true, true, float, float, 3>(H, stream);
         launch_dma<128, 128, 2, 2, true, true, float, float, 3>(T, stream);
         CATQ_CHECK_LAUNCH("gemm factor epilogue");

@@ -1,0 +1,93 @@
+"""Linear layers whose extents are no tile multiples in any direction: the
+direct-to-LDS products with ragged columns of a K-major operand, a ragged
+contraction of a K-contiguous one, and the factor epilogue on partial tiles,
+against plain float64 products and the oracle's factor gradients."""
+import numpy as np
+import pytest
+
+import synthgen as sg
+from helpers import f64, host, max_norm_err, to_dev_bf16, to_dev_f32
+from oracle import lmst
+
+pytestmark = pytest.mark.gpu
+
+# bf16 outputs: one rounding, at most 2^-9 of the value, and fp32 sums of
+# exact products far below that
+BF16 = 2.0 ** -8
+
+
+def _case(catq, M, N, K, mode=lmst.SOFT, E=1, off=None, nan_row=None):
+    import torch
+    xb = sg.normal_bf16(21, "X", (M, K))
+    wb = sg.normal_bf16(21, "W", (E * N, K), std=0.02)
+    dyb = sg.normal_bf16(21, "Y", (M, N), std=1e-3)
+    if nan_row is not None:
+        dyb[nan_row] = 0x7FC0
+    X, W, dY = to_dev_bf16(xb), to_dev_bf16(wb), to_dev_bf16(dyb)
+    ng = E * N * K // 128
+    fac = sg.perturbed_factors(22, ng)
+    dm, da, dd = (to_dev_f32(f) for f in fac)
+    stats = torch.zeros(ng, 2, dtype=torch.float32, device="cuda")
+    wf = torch.empty_like(W)
+    p = catq.lmst_params(mode=mode, s=7.0, s_bwd=30.0)
+    catq.catq_modulate_ternarize(W, dm, da, dd, p, stats, 0, W_fake=wf)
+    ws = torch.empty(catq.catq_workspace_size(0, M, N, K, E), dtype=torch.uint8, device="cuda")
+    kw = dict(n_experts=E, row_offsets=torch.tensor(off, device="cuda")) if E > 1 else {}
+    # outputs inside larger buffers: nothing may be written past their ends
+    Yb = torch.full((M * N + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+    dXb = torch.full((M * K + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+    g = [torch.full((ng + 16,), 7.0, dtype=torch.float32, device="cuda") for _ in range(3)]
+    catq.catq_fakeq_linear_fwd(X, wf, Yb[:M * N].view(M, N), M, N, K, **kw)
+    catq.catq_fakeq_linear_bwd(dY, X, wf, M, N, K, W, stats, dm, da, dd, p, *[t[:ng] for t in g], ws,
+                               dX=dXb[:M * K].view(M, K), **kw)
+    torch.cuda.synchronize()
+    for t, n in [(Yb, M * N), (dXb, M * K)] + [(t, ng) for t in g]:
+        assert bool((t[n:] == 7.0).all())
+    off = off or [0, M]
+    Wf = host(wf.float()).astype(np.float64).reshape(E, N, K)
+    X64, dY64 = f64(xb), f64(dyb)
+    Y, dX, G = np.zeros((M, N)), np.zeros((M, K)), np.zeros((E, N, K))
+    for e in range(E):
+        r = slice(off[e], off[e + 1])
+        Y[r], dX[r], G[e] = X64[r] @ Wf[e].T, dY64[r] @ Wf[e], dY64[r].T @ X64[r]
+    got = (host(Yb[:M * N].float()).reshape(M, N), host(dXb[:M * K].float()).reshape(M, K),
+           [host(t[:ng]) for t in g])
+    ref = lmst.factor_grads(G.reshape(E * N, K), f64(wb), 128, *fac, mode, s=7.0, s_bwd=30.0)
+    return got, (Y, dX, ref)
+
+
+@pytest.mark.parametrize("mode", [lmst.SOFT, lmst.HARD])
+@pytest.mark.parametrize("M,N,K", [
+    (8, 8, 128),          # one partial tile in every direction
+    (130, 264, 128),      # a tile and a remainder; ragged contraction of dX (264)
+    (65, 1032, 640),      # one token past a k tile; d_in = 2.5 tiles of 256
+    (1000, 1048, 1152),   # 128-wide tiles, token remainder 40
+    (999, 4104, 2688),    # 256-wide tiles with remainders, odd tokens
+    (4100, 4104, 2688),   # the same with a partial last round
+])
+def test_ragged_dense(catq, M, N, K, mode):
+    (y, dx, g), (Y, dX, G) = _case(catq, M, N, K, mode)
+    assert max_norm_err(y, Y) <= BF16
+    assert max_norm_err(dx, dX) <= BF16
+    for a, b in zip(g, G):
+        assert max_norm_err(a, b) <= 1e-3
+
+
+@pytest.mark.parametrize("N,K", [(264, 384), (1032, 128)])
+def test_ragged_experts(catq, N, K):
+    off = [0, 0, 70, 71, 400, 520]   # an empty expert, one row, remainders
+    (y, dx, g), (Y, dX, G) = _case(catq, 520, N, K, E=5, off=off)
+    assert max_norm_err(y, Y) <= BF16
+    assert max_norm_err(dx, dX) <= BF16
+    for a, b in zip(g, G):
+        assert max_norm_err(a, b) <= 1e-3
+
+
+@pytest.mark.parametrize("M,N,K", [(130, 264, 256), (700, 4104, 2688)])
+def test_nan_row_stays_in_its_row(catq, M, N, K):
+    """dY rows are the ragged contraction operand of dX: the last chunk of row
+    r - 1 must not pick up the first values of a NaN row r."""
+    import torch  # noqa: F401
+    (_, dx, _), _ = _case(catq, M, N, K, nan_row=67)
+    bad = ~np.isfinite(dx).all(1)
+    assert list(np.nonzero(bad)[0]) == [67]
