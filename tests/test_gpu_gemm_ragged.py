@@ -91,3 +91,37 @@ def test_nan_row_stays_in_its_row(catq, M, N, K):
     (_, dx, _), _ = _case(catq, M, N, K, nan_row=67)
     bad = ~np.isfinite(dx).all(1)
     assert list(np.nonzero(bad)[0]) == [67]
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 8, 128),        # one group, most waves without work
+    (33, 40, 128),      # remainders of a 32 x 32 tile, contraction of 40 and 33
+    (1021, 72, 384),    # odd token contraction over eight waves
+    (2100, 136, 128),   # token contraction split in two
+    (2049, 1032, 256),  # 64 x 64 tiles with remainders
+])
+def test_f32_linear(catq, M, N, K):
+    """The fp32 product in its three layouts (residual in the forward) against
+    float64: errors of an fp32 sum of up to 2100 terms, 2^-24 * sqrt(2100) =
+    3e-6 of the largest output."""
+    import torch
+    x, w, dy, r = (sg.uniform_f32(31, n, s) for n, s in
+                   (("X", (M, K)), ("W", (N, K)), ("Y", (M, N)), ("G", (M, N))))
+    X, W, dY, R = (to_dev_f32(t) for t in (x, w, dy, r))
+    ng = N * K // 128
+    dm, da, dd = (to_dev_f32(f) for f in sg.perturbed_factors(32, ng))
+    stats = torch.zeros(ng, 2, dtype=torch.float32, device="cuda")
+    wf = torch.empty_like(W)
+    p = catq.lmst_params(mode=lmst.SOFT, s=7.0)
+    catq.catq_modulate_ternarize(W, dm, da, dd, p, stats, 0, W_fake=wf)
+    Y, dX = torch.empty_like(R), torch.empty_like(X)
+    dW = torch.empty_like(W)
+    g = [torch.empty(ng, dtype=torch.float32, device="cuda") for _ in range(3)]
+    ws = torch.empty(catq.catq_workspace_size(0, M, N, K), dtype=torch.uint8, device="cuda")
+    catq.catq_fakeq_linear_fwd(X, wf, Y, M, N, K, residual=R)
+    catq.catq_fakeq_linear_bwd(dY, X, wf, M, N, K, W, stats, dm, da, dd, p, *g, ws, dX=dX, dW_fake=dW)
+    torch.cuda.synchronize()
+    w64 = host(wf)
+    assert max_norm_err(host(Y), host(X) @ w64.T + host(R)) <= 3e-6
+    assert max_norm_err(host(dX), host(dY) @ w64) <= 3e-6
+    assert max_norm_err(host(dW), host(dY).T @ host(X)) <= 3e-6
