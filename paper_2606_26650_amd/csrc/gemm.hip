@@ -60,6 +60,7 @@ struct GemmLaunch {
   int64_t c_split_stride;
   int32_t tiles_m, tiles_n;
   int32_t group_m;  // tile rows per band of the tile walk (band_coords)
+  int32_t r_f32;    // the residual R is fp32 (gemm_few_kernel)
 };
 
 constexpr int LDS_PAD = 8;
@@ -392,7 +393,8 @@ __device__ __forceinline__ void store4f(bf16* p, f32x4 v) {
 //   covers all 16 bank groups once.  Rows past the matrix read as zero
 //   (their results are never stored).
 // * K-major ("km", stored [K][cols]): a tile is 64 rows of k x COLS bf16;
-//   chunk c of row k sits in slot k*(COLS/8) + (c ^ (4*(k & 3))).  Fragments
+//   chunk c of row k sits in slot k*(COLS/8) + (c ^ (4*(k & 3))) (64
+//   columns: c ^ (4*((k >> 1) & 1))).  Fragments
 //   come from two ds_read_b64_tr_b16 each: within a block of 16 lanes, lane i
 //   receives element e of its 4 values from the lanes 4e..4e+3, column i mod 4
 //   of their 8-byte rows.  When those four lanes point at row k0+e, columns
@@ -501,6 +503,13 @@ struct DmaOpKM {
   static constexpr int NI = 64 * CPR / 64 / NW;    // instructions per wave
   static constexpr int P = RPI >= 4 ? 1 : 4 / RPI; // period of the swizzle in i
   static constexpr int READS = 2;
+  // XOR on the chunk index of row k: the 4 rows x 64 B read together fall on
+  // four 64-byte windows of the 256 bytes of banks (128-byte rows of a
+  // 64-column tile: two rows cover them already)
+  static __device__ __forceinline__ int swz(int row) {
+    return CPR >= 16 ? 4 * (row & 3) : 4 * ((row >> 1) & 1);
+  }
+  static_assert(CPR >= 8, "tile too narrow for the swizzle");
   static_assert(NI >= 1 && RPI >= 1 && NI % P == 0, "tile too small for the wave count");
   const char* panel;     // byte address of the tile's first column, row 0 (uniform)
   uint32_t ld2;          // row pitch in bytes
@@ -516,7 +525,7 @@ struct DmaOpKM {
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int row = (wave * NI + p) * RPI + lane / CPR;
-      const int c = (lane % CPR) ^ (4 * (row & 3));
+      const int c = (lane % CPR) ^ swz(row);
       voff[p] = (uint32_t)(row * ld * 2 + c * 16);
     }
   }
@@ -544,7 +553,7 @@ struct DmaOpKM {
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const int row = kk * 16 + 8 * (blk >> 1) + 4 * c + (s >> 2);
-      const int chunk = (col >> 3) ^ (4 * (row & 3));
+      const int chunk = (col >> 3) ^ swz(row);
       const short* p = reinterpret_cast<const short*>(lds) + row * COLS + chunk * 8 + (col & 7);
       const lds_v4s v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
           (__attribute__((address_space(3))) lds_v4s*)(p));
@@ -587,34 +596,24 @@ __device__ __forceinline__ bool group_tile(const int64_t* off, int E, int t, int
   return found;
 }
 
-template <int BM, int BN, int WGM, int WGN, bool AKM, bool BKM, typename OutT, typename RT,
-          bool HAS_R, int EPI = 0, int SB = 2, bool KR = false>
-__global__ __launch_bounds__(WGM* WGN * 64, 1)
-    __attribute__((amdgpu_waves_per_eu(1, (WGM * WGN + 3) / 4))) void gemm_dma_kernel(GemmLaunch L) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int NW = WGM * WGN;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int FM = WTM / 32, FN = WTN / 32;
-  static_assert(FM >= 1 && FN >= 1 && FM * FN >= FM + FN, "bad tile");
-  using OA = std::conditional_t<AKM, DmaOpKM<BM, NW>, DmaOpNT<BM, NW, KR>>;
-  using OB = std::conditional_t<BKM, DmaOpKM<BN, NW>, DmaOpNT<BN, NW, KR>>;
-  // one LDS allocation: the two stages of A, then the SB of B (the epilogue
-  // stages the output through the first two stages' worth of it).  SB = 3
-  // puts B's copies two k tiles ahead, for B streamed from HBM once (a large
-  // weight, or an expert's weight used by one row tile)
-  static_assert(SB == 2 || SB == 3, "two or three B stages");
-  constexpr int LDS_SLOTS = 2 * (BM + BN) * 8;
-  __shared__ uint4 smem[(2 * BM + SB * BN) * 8];
-  auto sA = [&](int buf) { return smem + buf * (BM * 8); };
-  auto sB = [&](int buf) { return smem + 2 * BM * 8 + buf * (BN * 8); };
+// Where a workgroup of the direct-to-LDS kernels works: its tile (first row
+// of A and C, column tile), the rows of A and C that are valid, its
+// contraction range, its B and the offset of its C.
+struct TilePlace {
+  int pn, z;
+  int64_t m0, m_lim, kb, ke, c_off;
+  const bf16* B;
+};
+template <int BM>
+__device__ __forceinline__ bool place_tile(const GemmLaunch& L, int lane, TilePlace& t) {
   const GemmArgs& g = L.g;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WGN, wn = wave % WGN;
-  int pm = 0, pn = 0, z = 0;
-  int64_t m0, m_lim = g.M;   // first row of A (rows) and C of the tile; rows below m_lim valid
-  int64_t kb = 0, ke = g.K, c_off = 0;
-  const bf16* Bb = reinterpret_cast<const bf16*>(g.B);
+  int pm = 0;
+  t.pn = t.z = 0;
+  t.m_lim = g.M;
+  t.kb = 0;
+  t.ke = g.K;
+  t.c_off = 0;
+  t.B = reinterpret_cast<const bf16*>(g.B);
   if (g.group_mode == 1) {
     // rows grouped by expert; blocks past the experts' tiles leave at once
     // (uniformly: every wave computes the same search)
@@ -623,7 +622,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
     group_tile(g.group_off, g.n_groups, t0, BM, lane, e, pt, tiles);
     const int n_real = tiles * L.tiles_n;
     const int lin = blockIdx.x;
-    if (lin >= n_real) return;
+    if (lin >= n_real) return false;
     // Each XCD (round-robin dispatch) takes a contiguous range of the real
     // tile ids, ordered expert by expert, then n-tile, then m-tile: the few
     // m-tiles of an expert that share one of its weight panels run back to
@@ -632,28 +631,63 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
     const int v = x * q + min(x, r) + (lin >> 3);
     group_tile(g.group_off, g.n_groups, v / L.tiles_n, BM, lane, e, pt, tiles);
     const int64_t r0 = g.group_off[e];
-    m_lim = g.group_off[e + 1];
-    const int te = (int)((m_lim - r0 + BM - 1) / BM);              // the expert's m-tiles
+    t.m_lim = g.group_off[e + 1];
+    const int te = (int)((t.m_lim - r0 + BM - 1) / BM);            // the expert's m-tiles
     const int local = v - (v / L.tiles_n - pt) * L.tiles_n;        // id within the expert
-    pn = local / te;
-    m0 = r0 + (int64_t)(local - pn * te) * BM;
-    Bb += (int64_t)e * g.b_gs;
+    t.pn = local / te;
+    t.m0 = r0 + (int64_t)(local - t.pn * te) * BM;
+    t.B += (int64_t)e * g.b_gs;
   } else {
     split_tile_coords(blockIdx.x, L.tiles_m, L.tiles_n,
-                      g.group_mode == 2 ? g.n_groups : L.ksplit, pm, pn, z, L.group_m);
-    m0 = (int64_t)pm * BM;
+                      g.group_mode == 2 ? g.n_groups : L.ksplit, pm, t.pn, t.z, L.group_m);
+    t.m0 = (int64_t)pm * BM;
     if (g.group_mode == 2) {
       // contraction grouped by expert (ragged): rows past the group's end
       // read as zero; an empty group writes a zero tile
-      kb = g.group_off[z];
-      ke = g.group_off[z + 1];
-      c_off = (int64_t)z * g.c_gs;
+      t.kb = g.group_off[t.z];
+      t.ke = g.group_off[t.z + 1];
+      t.c_off = (int64_t)t.z * g.c_gs;
     } else if (L.ksplit > 1) {
-      kb = (int64_t)z * L.kchunk;
-      ke = min(g.K, kb + L.kchunk);
-      c_off = (int64_t)z * L.c_split_stride;
+      t.kb = (int64_t)t.z * L.kchunk;
+      t.ke = min(g.K, t.kb + L.kchunk);
+      t.c_off = (int64_t)t.z * L.c_split_stride;
     }
   }
+  return true;
+}
+
+template <int BM, int BN, int WGM, int WGN, bool AKM, bool BKM, typename OutT, typename RT,
+          bool HAS_R, int EPI = 0, int SB = 2, bool KR = false>
+__global__ __launch_bounds__(WGM* WGN * 64, 1)
+    __attribute__((amdgpu_waves_per_eu(1, (WGM * WGN + 3) / 4))) void gemm_dma_kernel(GemmLaunch L) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int NW = WGM * WGN;
+  constexpr int WTM = BM / WGM, WTN = BN / WGN;
+  constexpr int FM = WTM / 32, FN = WTN / 32;
+  static_assert(FM >= 1 && FN >= 1, "bad tile");
+  using OA = std::conditional_t<AKM, DmaOpKM<BM, NW>, DmaOpNT<BM, NW, KR>>;
+  using OB = std::conditional_t<BKM, DmaOpKM<BN, NW>, DmaOpNT<BN, NW, KR>>;
+  // one LDS allocation: the two stages of A, then the SB of B (the epilogue
+  // stages the output through the first two stages' worth of it).  SB = 3
+  // puts B's copies two k tiles ahead, for B streamed from HBM once (a large
+  // weight, or an expert's weight used by one row tile).  SB = 4:
+  // four stages of both operands, copies three k tiles ahead, for launches of
+  // at most one workgroup per compute unit
+  static_assert(SB >= 2 && SB <= 4, "two to four B stages");
+  constexpr int SA = SB == 4 ? 4 : 2;
+  constexpr int LDS_SLOTS = 2 * (BM + BN) * 8;
+  __shared__ uint4 smem[(SA * BM + SB * BN) * 8];
+  auto sA = [&](int buf) { return smem + buf * (BM * 8); };
+  auto sB = [&](int buf) { return smem + SA * BM * 8 + buf * (BN * 8); };
+  const GemmArgs& g = L.g;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  TilePlace t;
+  if (!place_tile<BM>(L, lane, t)) return;
+  const int pn = t.pn, z = t.z;
+  const int64_t m0 = t.m0, m_lim = t.m_lim, kb = t.kb, ke = t.ke, c_off = t.c_off;
+  const bf16* Bb = t.B;
   const int64_t n0 = (int64_t)pn * BN;
   OA oa;
   OB ob;
@@ -664,10 +698,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
     ob.init(Bb, g.ldb, n0, g.N, wave, lane);
   oa.bind(kb, ke);
   ob.bind(kb, ke);
-  // LDS byte address of the operand stages (uniform): A's two, then B's SB
+  // LDS byte address of the operand stages (uniform): A's SA, then B's SB
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)smem;
   bf16x8 fa[2][FM], fb[2][FN];
-  // stages by index: A's is the k tile's parity, B's is carried along (kt % SB)
+  // stages by index: A's is kt % SA, B's is carried along (kt % SB)
   auto ldfrag = [&](int ast, int bst, int kk, int slot) {
 #pragma unroll
     for (int i = 0; i < FM; ++i) fa[slot][i] = oa.frag(sA(ast), wm * WTM + 32 * i, kk, lane);
@@ -675,10 +709,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
     for (int j = 0; j < FN; ++j) fb[slot][j] = ob.frag(sB(bst), wn * WTN + 32 * j, kk, lane);
   };
   auto issueA = [&](int kt) {
-    oa.issue(lds0 + (uint32_t)(kt & 1) * (BM * 128), kb + (int64_t)kt * 64, wave);
+    oa.issue(lds0 + (uint32_t)(kt & (SA - 1)) * (BM * 128), kb + (int64_t)kt * 64, wave);
   };
   auto issueB = [&](int kt, int bst) {
-    ob.issue(lds0 + 2 * BM * 128 + (uint32_t)bst * (BN * 128), kb + (int64_t)kt * 64, wave);
+    ob.issue(lds0 + SA * BM * 128 + (uint32_t)bst * (BN * 128), kb + (int64_t)kt * 64, wave);
   };
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -719,22 +753,26 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
     // copies of tile kt+1 (A; and B with two stages) or kt+2 (B, three
     // stages) into the stages tile kt-1 used; B's copies are issued last, so
     // with three stages waiting for all but B's newest finishes tile kt+1
-    if (MORE) issueA(kt + 1);
+    // (four stages: of tile kt+3, in the stages tile kt-1 used)
+    if (SB < 4 && MORE) issueA(kt + 1);
     if (SB == 2 && MORE) issueB(kt + 1, bnext);
-    const bool deep = SB == 3 && kt + 2 < nk;
-    if (deep) issueB(kt + 2, bst == 0 ? SB - 1 : bst - 1);   // (kt + 2) % 3
+    const bool deep = SB > 2 && kt + SB - 1 < nk;
+    if (SB == 4 && deep) issueA(kt + 3);
+    if (deep) issueB(kt + SB - 1, bst == 0 ? SB - 1 : bst - 1);   // (kt + SB - 1) % SB
 #pragma unroll
     for (int kk = 0; kk < 3; ++kk) {
-      ldfrag(kt & 1, bst, kk + 1, (kk & 1) ^ 1);
+      ldfrag(kt & (SA - 1), bst, kk + 1, (kk & 1) ^ 1);
       mfmas(kk & 1);
       interleave();
     }
     if (deep)
-      wait_vmem_n<OB::NI>();
+      wait_vmem_n<SB == 4 ? 2 * (OA::NI + OB::NI) : OB::NI>();
+    else if (SB == 4 && kt + 2 < nk)
+      wait_vmem_n<SB == 4 ? OA::NI + OB::NI : 0>();
     else
       wait_vmem();
     __syncthreads();
-    if (MORE) ldfrag((kt + 1) & 1, bnext, 0, 0);
+    if (MORE) ldfrag((kt + 1) & (SA - 1), bnext, 0, 0);
     mfmas(1);
     if (MORE) interleave();
   };
@@ -759,6 +797,16 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
     if (SB == 3 && nk > 1) {
       issueB(1, 1);
       wait_vmem_n<OB::NI>();
+    } else if (SB == 4 && nk > 2) {
+      issueA(1);
+      issueB(1, 1);
+      issueA(2);
+      issueB(2, 2);
+      wait_vmem_n<SB == 4 ? 2 * (OA::NI + OB::NI) : 0>();
+    } else if (SB == 4 && nk > 1) {
+      issueA(1);
+      issueB(1, 1);
+      wait_vmem_n<SB == 4 ? OA::NI + OB::NI : 0>();
     } else {
       wait_vmem();
     }
@@ -1079,6 +1127,149 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
 #endif
 }
 
+// -------------------------------------------------- few output tiles
+// Problems with too few 128 x 128 tiles to fill the chip (short token counts,
+// small layers): what bounds them is the latency of each k tile on the few
+// compute units that work (0.7 us on 128 x 128 tiles, one k tile of copies in
+// flight, against 0.2 us of products).  So this kernel spreads the output
+// over BM x BN tiles of half that size, keeps S - 1 k tiles of copies in
+// flight, and lets its four waves split each 64-deep k tile:
+// wave w multiplies the whole tile over k = 16 w .. 16 w + 15, so a fragment
+// is read from LDS by one wave only.  The four partial tiles are summed
+// through LDS in wave order.  Operand tiles, their swizzles and the bounds of
+// ragged extents are those of the kernel above.
+template <int BM, int BN, int S, bool AKM, bool BKM, typename OutT>
+__global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int NW = 4, FM = BM / 32, FN = BN / 32;
+  using OA = std::conditional_t<AKM, DmaOpKM<BM, NW>, DmaOpNT<BM, NW, true>>;
+  using OB = std::conditional_t<BKM, DmaOpKM<BN, NW>, DmaOpNT<BN, NW, true>>;
+  constexpr int NI = OA::NI + OB::NI;              // copies per wave and k tile
+  constexpr int STAGE = (BM + BN) * 8;             // 16-byte slots of a stage
+  constexpr int EP = BN + 8;                       // pitch of the partial tiles (floats)
+  constexpr int SLOTS = S * STAGE > NW * BM * EP / 4 ? S * STAGE : NW * BM * EP / 4;
+  __shared__ uint4 smem[SLOTS];
+  const GemmArgs& g = L.g;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  TilePlace t;
+  if (!place_tile<BM>(L, lane, t)) return;
+  const int64_t n0 = (int64_t)t.pn * BN;
+  OA oa;
+  OB ob;
+  oa.init(reinterpret_cast<const bf16*>(g.A), g.lda, t.m0, t.m_lim, wave, lane);
+  ob.init(t.B, g.ldb, n0, g.N, wave, lane);
+  oa.bind(t.kb, t.ke);
+  ob.bind(t.kb, t.ke);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)smem;
+  const int nk = (int)((t.ke - t.kb + 63) / 64);
+  auto issue = [&](int kt, int st) {
+    oa.issue(lds0 + (uint32_t)st * (STAGE * 16), t.kb + (int64_t)kt * 64, wave);
+    ob.issue(lds0 + (uint32_t)st * (STAGE * 16) + BM * 128, t.kb + (int64_t)kt * 64, wave);
+  };
+  f32x16 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
+#pragma unroll
+  for (int q = 0; q < S - 1; ++q)
+    if (q < nk) issue(q, q);
+  int st = 0;
+  // Tile kt is multiplied while the fragments of tile kt + 1 are read (two
+  // register sets): wait for tile kt's copies, barrier, issue the copies of
+  // tile kt + S - 1, read tile kt's fragments, multiply tile kt - 1.
+  bf16x8 fa[2][FM], fb[2][FN];
+  auto mul = [&](auto slot_c) {
+    constexpr int s = decltype(slot_c)::value;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][i], fb[s][j], acc[i][j], 0, 0, 0);
+  };
+  auto step = [&](int kt, auto slot_c) {
+    constexpr int s = decltype(slot_c)::value;
+    // tile kt has landed when only the copies of the tiles after it (at most
+    // S - 2 of those issued) are outstanding
+    const int behind = min(S - 2, nk - 1 - kt);
+    if (behind == S - 2)
+      wait_vmem_n<(S - 2) * NI>();
+    else if (S > 3 && behind == S - 3)
+      wait_vmem_n<(S > 3 ? S - 3 : 0) * NI>();
+    else
+      wait_vmem();
+    // every wave has also read its fragments of tile kt - 1, whose stage the
+    // next copies take
+    __syncthreads();
+    if (kt + S - 1 < nk) issue(kt + S - 1, st == 0 ? S - 1 : st - 1);
+    const uint4* a = smem + st * STAGE;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) fa[s][i] = oa.frag(a, 32 * i, wave, lane);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) fb[s][j] = ob.frag(a + BM * 8, 32 * j, wave, lane);
+    if (kt > 0) mul(std::integral_constant<int, 1 - s>{});
+    st = st + 1 == S ? 0 : st + 1;
+  };
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  int kt = 0;
+  for (; kt + 1 < nk; kt += 2) {
+    step(kt, S0{});
+    step(kt + 1, S1{});
+  }
+  if (kt < nk) {
+    step(kt, S0{});
+    mul(S0{});
+  } else if (nk > 0) {
+    mul(S1{});
+  }
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        red[(wave * BM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * EP + 32 * j + (lane & 31)] =
+            acc[i][j][r];
+  __syncthreads();
+  OutT* C = reinterpret_cast<OutT*>(g.C) + t.c_off;
+  constexpr int LPR = BN / 4, RPP = 256 / LPR;   // lanes per row, rows per pass
+  const int cc = (tid % LPR) * 4;
+  const int64_t n = n0 + cc;
+  const bool vec = g.N % 4 == 0 && g.ldc % 4 == 0 && t.c_off % 4 == 0 && aligned16(C) &&
+                   (!g.R || (g.ldr % 4 == 0 && aligned16(g.R)));
+#pragma unroll
+  for (int q = 0; q < BM / RPP; ++q) {
+    const int rr = q * RPP + tid / LPR;
+    const int64_t m = t.m0 + rr;
+    if (m >= t.m_lim || n >= g.N) continue;
+    f32x4 v = *reinterpret_cast<const f32x4*>(red + rr * EP + cc);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4*>(red + (w * BM + rr) * EP + cc);
+    v *= g.alpha;
+    if (vec) {
+      if (g.R)
+        v += L.r_f32 ? load4f(reinterpret_cast<const float*>(g.R) + m * g.ldr + n)
+                     : load4f(reinterpret_cast<const bf16*>(g.R) + m * g.ldr + n);
+      store4f(C + m * g.ldc + n, v);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (n + e >= g.N) break;
+        float x = v[e];
+        if (g.R)
+          x += L.r_f32 ? reinterpret_cast<const float*>(g.R)[m * g.ldr + n + e]
+                       : to_f(reinterpret_cast<const bf16*>(g.R)[m * g.ldr + n + e]);
+        store_out<OutT>(C + m * g.ldc + n + e, x);
+      }
+    }
+  }
+#endif
+}
+
 // ------------------------------------------------------------- fp32 GEMM
 // fp32 problems (the fp32 single-linear workload) on v_mfma_f32_32x32x2_f32:
 // products and sums in fp32, like an FMA chain.  What bounds these small
@@ -1281,7 +1472,7 @@ static void launch_dma(GemmLaunch& L, hipStream_t stream) {
                 BN, WGM, WGN, AKM ? "k" : "n", BKM ? "k" : "t", tname<OutT>(), tname<RT>(),
                 g.R ? "true" : "false",
                 EPI == 1 ? ", swiglu" : (EPI == 2 ? ", swiglu_bwd" : (EPI == 3 ? ", factor_grads" : "")),
-                g.group_mode ? ", experts" : "", SB == 3 ? ", 3 B stages" : "",
+                g.group_mode ? ", experts" : "", SB == 3 ? ", 3 B stages" : (SB == 4 ? ", 4 stages" : ""),
                 KR ? ", ragged k" : "");
   double flops, bytes;
   gemm_work(L, (int)sizeof(OutT), flops, bytes);
@@ -1299,6 +1490,25 @@ static void launch_dma(GemmLaunch& L, hipStream_t stream) {
     CATQ_TRACED(stream, tag, flops, bytes, g.M, g.N, g.K,
                 hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, AKM, BKM, OutT, RT, false, EPI, SB, KR>),
                                    grid, block, 0, stream, L));
+}
+
+template <int BM, int BN, int S, int A_T, int B_T, typename OutT, typename RT>
+static void launch_few(GemmLaunch& L, hipStream_t stream) {
+  const GemmArgs& g = L.g;
+  L.group_m = 8;
+  L.r_f32 = sizeof(RT) == 4;
+  // grouped rows: at most ceil(M/BM) + E m-tiles over all experts together
+  L.tiles_m = (int)((g.M + BM - 1) / BM) + (g.group_mode == 1 ? g.n_groups : 0);
+  L.tiles_n = (int)((g.N + BN - 1) / BN);
+  const dim3 grid((unsigned)(L.tiles_m * L.tiles_n * (g.group_mode == 2 ? g.n_groups : L.ksplit)));
+  char tag[96];
+  std::snprintf(tag, sizeof(tag), "gemm_few_kernel<%d, %d, %d, %s%s, %s>%s", BM, BN, S, A_T ? "k" : "n",
+                B_T ? "k" : "t", tname<OutT>(), g.group_mode ? ", experts" : "");
+  double flops, bytes;
+  gemm_work(L, (int)sizeof(OutT), flops, bytes);
+  CATQ_TRACED(stream, tag, flops, bytes, g.M, g.N, g.K,
+              hipLaunchKernelGGL((gemm_few_kernel<BM, BN, S, A_T == 1, B_T == 1, OutT>), grid,
+                                 dim3(256), 0, stream, L));
 }
 
 // The direct-to-LDS kernel serves every unbatched bf16 problem whose row
@@ -1423,6 +1633,24 @@ static void launch_bf16(GemmLaunch& L, hipStream_t stream) {
     return;
   }
   if (g.group_mode == 0 && dma_ok(L, A_T, B_T)) {
+    // Too few 128 x 128 tiles for two per compute unit: 64 x 64 tiles while
+    // those are at most two per unit, then 128 x 128 tiles on eight waves with
+    // four stages while there is at most one per unit.  Measured at 128 x 128 /
+    // 64 x 64 / four stages: 512 x 2048 outputs, contraction 4096 (256 tiles of
+    // 64) 43 / 20 / 31 us; 1000 x 2048 over 2048 (512) 25 / 17 / 19; 1500 x 2048
+    // over 2048 (768; 192 of 128) 25 / 26 / 20; 1000 x 4096 over 4096 (256 of
+    // 128) 46 / 51 / 38; 1400 x 3072 over 2048 (264 of 128) 28 / 38 / 37.
+    if constexpr (!(A_T == 1 && B_T == 0)) {
+      auto tiles = [&](int64_t t) { return ((g.M + t - 1) / t) * ((g.N + t - 1) / t) * L.ksplit; };
+      if (tiles(64) <= 512) {
+        launch_few<64, 64, 4, A_T, B_T, OutT, RT>(L, stream);
+        return;
+      }
+      if (tiles(128) <= 256) {
+        launch_dma<128, 128, 2, 4, A_T == 1, B_T == 1, OutT, RT, 0, 4>(L, stream);
+        return;
+      }
+    }
     launch_dma<128, 128, 2, 2, A_T == 1, B_T == 1, OutT, RT>(L, stream);
     return;
   }
@@ -1560,7 +1788,12 @@ catq_status gemm_run_factor(const GemmArgs& a, hipStream_t stream) {
     // fewer tiles than fill the chip: 128 x 128 (4096 x 2048 weights over 512
     // tokens: 36 us on 128 tiles of 256 x 256, 29 us on 512 of 128 x 128)
     if (tm * tn < kTiles256) {
-      launch_dma<128, 128, 2, 2, true, true, float, float, 3>(L, stream);
+      // (at most one per compute unit: four stages, 24.4 -> 22.2 us on 2048 x
+      // 2048 weights over 1000 tokens)
+      if (((a.M + 127) / 128) * (a.N / 128) <= 256)
+        launch_dma<128, 128, 2, 2, true, true, float, float, 3, 4>(L, stream);
+      else
+        launch_dma<128, 128, 2, 2, true, true, float, float, 3>(L, stream);
       CATQ_CHECK_LAUNCH("gemm factor epilogue");
       return CATQ_OK;
     }

@@ -61,7 +61,12 @@ def _case(catq, M, N, K, mode=lmst.SOFT, E=1, off=None, nan_row=None):
     (8, 8, 128),          # one partial tile in every direction
     (130, 264, 128),      # a tile and a remainder; ragged contraction of dX (264)
     (65, 1032, 640),      # one token past a k tile; d_in = 2.5 tiles of 256
-    (1000, 1048, 1152),   # 128-wide tiles, token remainder 40
+    (1000, 1048, 1152),   # 64-wide tiles over 16 k tiles, token remainder 40
+    (1000, 3080, 2176),   # 128-wide tiles in four stages (forward), 34 k tiles
+    (1500, 2104, 128),    # the same with two k tiles
+    (1500, 64, 2176),     # and with one, in the input gradient
+    (1500, 136, 2176),    # and with three, the last ragged
+    (2100, 3080, 2176),   # 128-wide tiles, two per unit
     (999, 4104, 2688),    # 256-wide tiles with remainders, odd tokens
     (4100, 4104, 2688),   # the same with a partial last round
 ])
