@@ -932,13 +932,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
           }
         // the next part's weights, in flight while this part is processed
         if (p + 1 < PARTS) epi3_load(p + 1);
-        float sT = 0.f, s1 = 0.f, sW = 0.f, sD = 0.f;
+        FacSums sum = {0.f, 0.f, 0.f, 0.f};
         if (mrow + rr < m_lim && F.mode != CATQ_IDENTITY) {
           const float mu = gs.mu;
-          // z = (w - mu) / alpha * c2s as one FMA per weight
-          const float zk = F.st.c2s * __builtin_amdgcn_rcpf(gs.alpha_div), z0 = -mu * zk;
-          const float dz = gs.delta * F.st.c2s;
-          const float ed = one_minus_exp_neg(gs.delta * F.st.s4, gs.delta * F.st.s4l);
+          // z = (w - mu) / alpha * c2s as one FMA per weight (the scale bounded:
+          // with alpha near zero, a constant group, w and mu cancel to a finite z)
+          const float zk = fminf(F.st.c2s * __builtin_amdgcn_rcpf(gs.alpha_div), 1e30f);
+          const float z0 = -mu * zk;
+          const TransGroup tg = trans_group(gs.delta, F.st);
           // one pass: 4 weights (rotated into wv[0]) against 4 G values;
           // (HARD, STE: the straight-through estimator, hard mode only) are
           // launch constants, one loop per combination
@@ -951,41 +952,12 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
             wv[0] = wv[1];
             wv[1] = wv[2];
             wv[2] = wv[3];
-            float hc[4];
-            if constexpr (HARD) {
-              const float w4[4] = {w[0], w[1], w[2], w[3]};
-              hard_codes_n<4>(w4, mu, hard_thresh(gs.delta, gs.alpha_div), hc);
-            }
-            float z[4], E[4];
+            const float w4[4] = {w[0], w[1], w[2], w[3]}, v4[4] = {v[0], v[1], v[2], v[3]};
+            float hc[4] = {0.f, 0.f, 0.f, 0.f}, z[4];
+            if constexpr (HARD) hard_codes_n<4>(w4, mu, hard_thresh(gs.delta, gs.alpha_div), hc);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              z[e] = fmaf(w[e], zk, z0);
-              E[e] = 1.0f - __builtin_amdgcn_exp2f(-2.0f * fabsf(z[e]));
-            }
-            if constexpr (!STE) {
-              // 1 - 2^(-2y) by its series below y = 0.09 (no cancellation),
-              // only in passes where some lane of the wave has such a y
-              bool small = false;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) small |= fabsf(z[e]) < 0.09016844f;
-              if (__any(small)) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  const float y = fabsf(z[e]);
-                  E[e] = y < 0.09016844f ? one_minus_exp2_neg2(y, 0.0f) : E[e];
-                }
-              }
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              float fp = 0.f, fwp = 1.f, fdp = 0.f;
-              if constexpr (!STE) transition_parts_zE(z[e], dz, ed, E[e], fp, fwp, fdp);
-              sT = fmaf(v[e], HARD ? hc[e] : fp, sT);
-              const float gf = v[e] * fwp;
-              s1 += gf;
-              sW = fmaf(gf, z[e], sW);  // g f_W z: wz rescales per group
-              sD = fmaf(v[e], fdp, sD);
-            }
+            for (int e = 0; e < 4; ++e) z[e] = fmaf(w4[e], zk, z0);
+            fac_terms<4, HARD, STE>(v4, z, tg, hc, sum);
           };
           if (F.mode == CATQ_HARD && F.ste) {
 #pragma unroll 1
@@ -997,7 +969,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
 #pragma unroll 1
             for (int q = 0; q < 4; ++q) pass(q, std::false_type{}, std::false_type{});
           }
+          fac_finish(tg, sum);
         }
+        float sT = sum.T, s1 = sum.one, sW = sum.W, sD = sum.D;
 #pragma unroll
         for (int mk = 1; mk < 4; mk <<= 1) {
           sT += __shfl_xor(sT, mk, 64);

@@ -336,32 +336,26 @@ __global__ __launch_bounds__(256) void lmst_bwd_kernel(BwdArgs a) {
   }
   if (a.G_out) store8<float>(a.G_out + o * 8, G);
   GroupScalars gs = group_scalars(mu0, alpha0, fmu, fal, fde, a.delta0);
-  float ST = 0.f, SW = 0.f, S1 = 0.f, SD = 0.f;
+  FacSums sum = {0.f, 0.f, 0.f, 0.f};
   if (a.mode != CATQ_IDENTITY) {
     const float inv_a = 1.0f / gs.alpha_div;
-    const float dz = gs.delta * a.st.c2s;
-    const float ED = one_minus_exp_neg(gs.delta * a.st.s4, gs.delta * a.st.s4l);
-    float hc[8];
-    if (a.mode == CATQ_HARD) hard_codes8(w, gs.mu, hard_thresh(gs.delta, gs.alpha_div), hc);
+    const TransGroup tg = trans_group(gs.delta, a.st);
+    float hc[8], z[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      float xs = (w[j] - gs.mu) * inv_a;
-      float fp, fwp, fdp;
-      if (a.ste) {
-        fwp = 1.0f;
-        fdp = 0.0f;
-        fp = 0.0f;
-      } else {
-        transition_parts_z(xs, a.st.c2s, dz, ED, fp, fwp, fdp);
-      }
-      float T = (a.mode == CATQ_HARD) ? hc[j] : fp;
-      ST = fmaf(G[j], T, ST);
-      float gf = G[j] * fwp;
-      S1 += gf;
-      SW = fmaf(gf, xs, SW);
-      SD = fmaf(G[j], fdp, SD);
+      hc[j] = 0.0f;
+      z[j] = ((w[j] - gs.mu) * inv_a) * a.st.c2s;
     }
+    if (a.mode == CATQ_HARD) hard_codes8(w, gs.mu, hard_thresh(gs.delta, gs.alpha_div), hc);
+    if (a.mode == CATQ_HARD && a.ste)
+      fac_terms<8, true, true>(G, z, tg, hc, sum);
+    else if (a.mode == CATQ_HARD)
+      fac_terms<8, true, false>(G, z, tg, hc, sum);
+    else
+      fac_terms<8, false, false>(G, z, tg, hc, sum);
+    fac_finish(tg, sum);
   }
+  float ST = sum.T, S1 = sum.one, SW = sum.W, SD = sum.D;
   for (int m = L >> 1; m >= 1; m >>= 1) {
     ST += __shfl_xor(ST, m, 64);
     SW += __shfl_xor(SW, m, 64);
@@ -372,7 +366,7 @@ __global__ __launch_bounds__(256) void lmst_bwd_kernel(BwdArgs a) {
     // the constant factors of f (k2, soft only), f_W and f_Delta (sk4)
     const FacScale k = fac_scale(a.mode, a.ste, a.st);
     S1 *= k.w;
-    SW *= k.w;
+    SW *= k.wz;
     SD *= k.d;
     ST *= k.f;
     float v[3];

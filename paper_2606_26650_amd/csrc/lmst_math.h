@@ -105,43 +105,46 @@ __device__ __forceinline__ void hard_codes8(const float (&w)[8], float mu, const
   hard_codes_n<8>(w, mu, t, c);
 }
 
-// The softened ternarisation of one group in the base-2 exponent domain.
-// With z = (w - mu) * sc = 2 s W_hat log2(e), y = |z| and x = |W_hat|:
-//   q_a = e^{-2 s |x - Delta|} = 2^{-|y - dz|},   e^{-4 s x} = 2^{-2 y},
-//   E = 1 - e^{-4 s x},  q_b = q_a (1 - E) (x < Delta) or q_a (1 - E_Delta),
-//   alpha f = copysign(num / ((1 + q_a)(1 + q_b)), z) * alpha / tanh(s),
-//   num = E (x >= Delta) or q_a E (x < Delta)
-// (the cancellation-free form of Eq. 5; the scalings of the exponents and of
-// the output are folded into per-group constants).
-struct SoftGroup {
-  float mu;     // mu of Eq. 3
-  float sc;     // 2 s log2(e) / alpha:  z = (w - mu) * sc
-  float inv_a;  // 1 / alpha  (when sc does not fit a float)
-  float c2s;    // 2 s log2(e)
-  float dz;     // 2 s Delta log2(e)
-  float ed;     // E_Delta = 1 - e^{-4 s Delta}
-  float ak;     // alpha / tanh(s)
-  bool fast;    // sc finite: z in one product
-};
+// The transition function (Eq. 5) in the base-2 exponent domain.  With
+// z = 2 s log2(e) W_hat, t = 2^{-|z|} = e^{-2 s |W_hat|} and dz = 2 s log2(e) Delta,
+//   E = 1 - t^2,  D = 1 + 2 cosh(2 s Delta) t + t^2,
+//   f       = copysign(E / D, z) / tanh(s)
+//   f_W     = (2 s / tanh s) t (2 cosh(2 s Delta) (1 + t^2) + 4 t) / D^2
+//   f_Delta = -copysign((2 s / tanh s) 2 sinh(2 s Delta) t E / D^2, z)
+// (sinh(2u) / (cosh 2u + cosh 2d) = tanh(u - d) / 2 + tanh(u + d) / 2, and its
+// derivatives): sums of positive terms only, so no cancellation, and one
+// exponential and one reciprocal per weight.  The vector ALU is what bounds
+// the kernels that evaluate it (a form with exponentials of -|x - Delta| and
+// -2x and selects at |x| = Delta took ~12 more issue slots per weight for
+// f, ~16 for all three).  2 cosh must fit: a group with dz > kFastDz takes the
+// general form below, which has no such term.
+constexpr float kFastDz = 100.0f;
 
-__device__ __forceinline__ SoftGroup soft_group(const GroupScalars& gs, const StConst& c) {
-  SoftGroup q;
-  q.mu = gs.mu;
-  q.inv_a = __builtin_amdgcn_rcpf(gs.alpha_div);  // 1 ulp; W_hat needs no more
-  q.c2s = c.c2s;
-  q.sc = q.inv_a * c.c2s;
-  q.fast = fabsf(q.sc) <= 3.0e38f;  // false for inf and NaN
-  q.dz = gs.delta * c.c2s;
-  q.ed = one_minus_exp_neg(gs.delta * c.s4, gs.delta * c.s4l);
-  q.ak = gs.alpha * c.k2;
+// 2 cosh(2 s Delta) and 2 sinh(2 s Delta) (ed = 1 - e^{-4 s Delta}); the
+// exponent is formed in float64, so that its rounding (2^-24 of ~50) does not
+// enter f, whose dead zone is proportional to 1 / cosh.
+struct TransGroup {
+  float dz, ed, c2, s2;
+  bool fast;
+};
+__device__ __forceinline__ TransGroup trans_group(float delta, const StConst& c) {
+  TransGroup q;
+  const double e = (double)delta * (double)c.c2s, n = rint(e);
+  q.dz = (float)e;
+  q.ed = one_minus_exp_neg(delta * c.s4, delta * c.s4l);
+  q.fast = fabsf(q.dz) <= kFastDz;  // false for NaN
+  const float p = ldexpf(__builtin_amdgcn_exp2f((float)(e - n)), q.fast ? (int)n : 0);
+  q.c2 = p + __builtin_amdgcn_rcpf(p);
+  q.s2 = p * q.ed;
   return q;
 }
 
 // 1 - 2^{-2y} (= 1 - e^{-t}, t = 2 y ln 2) for y >= 0 given T = 2^{-2y}:
 // below t = 1/8 the series of 1 - e^{-t} to t^5 in powers of y (truncation
 // below 5e-8 relative), above it 1 - T (no cancellation: T < 0.89).
+constexpr float kSeriesY = 0.09016844f;
 __device__ __forceinline__ float one_minus_exp2_neg2(float y, float T) {
-  if (y < 0.09016844f) {
+  if (y < kSeriesY) {
     float p = 0.04266738519f;
     p = fmaf(p, y, -0.1538900584f);
     p = fmaf(p, y, 0.4440328777f);
@@ -152,87 +155,97 @@ __device__ __forceinline__ float one_minus_exp2_neg2(float y, float T) {
   return 1.0f - T;
 }
 
-// alpha * f(W_hat; s, Delta) of one weight (Eq. 5 times the group scale).
-template <bool FAST>
-__device__ __forceinline__ float soft_value(float w, const SoftGroup& q) {
-  const float z = FAST ? (w - q.mu) * q.sc : ((w - q.mu) * q.inv_a) * q.c2s;
+// t = 2^{-|z|} and E = 1 - t^2 of N weights; the series only where some lane of
+// the wave has a small |z| (a branch the compiler would otherwise turn into
+// the series for every weight).  The value does not depend on the branch.
+template <int N>
+__device__ __forceinline__ void exp_parts(const float (&z)[N], float (&t)[N], float (&E)[N]) {
+  float ym = fabsf(z[0]);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    t[j] = __builtin_amdgcn_exp2f(-fabsf(z[j]));
+    E[j] = fmaf(-t[j], t[j], 1.0f);
+    ym = fminf(ym, fabsf(z[j]));
+  }
+  if (__any(ym < kSeriesY)) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const float y = fabsf(z[j]);
+      E[j] = y < kSeriesY ? one_minus_exp2_neg2(y, 0.0f) : E[j];
+    }
+  }
+}
+
+// alpha * f(W_hat; s, Delta) of a group's weights (Eq. 5 times the scale).
+struct SoftGroup {
+  float mu;     // mu of Eq. 3
+  float sc;     // 2 s log2(e) / alpha:  z = (w - mu) * sc
+  float inv_a;  // 1 / alpha  (when sc does not fit a float)
+  float c2s;    // 2 s log2(e)
+  float ak;     // alpha / tanh(s)
+  TransGroup q;
+  bool fast;    // sc finite and 2 cosh fits
+};
+
+__device__ __forceinline__ SoftGroup soft_group(const GroupScalars& gs, const StConst& c) {
+  SoftGroup g;
+  g.mu = gs.mu;
+  g.inv_a = __builtin_amdgcn_rcpf(gs.alpha_div);  // 1 ulp; W_hat needs no more
+  g.c2s = c.c2s;
+  g.sc = g.inv_a * c.c2s;
+  g.ak = gs.alpha * c.k2;
+  g.q = trans_group(gs.delta, c);
+  g.fast = fabsf(g.sc) <= 3.0e38f && g.q.fast;  // false for inf and NaN
+  return g;
+}
+
+// The general form: with x = |W_hat|, y = |z|,
+//   q_a = e^{-2 s |x - Delta|} = 2^{-|y - dz|},  q_b = q_a (1 - E) (x < Delta) or
+//   q_a (1 - E_Delta),  f = copysign(num / ((1 + q_a)(1 + q_b)), z) / tanh(s),
+//   num = E (x >= Delta) or q_a E (x < Delta).
+__device__ __forceinline__ float soft_value_general(float w, const SoftGroup& g) {
+  const float z = ((w - g.mu) * g.inv_a) * g.c2s;
   const float y = fabsf(z);
-  const float d = y - q.dz;
+  const float d = y - g.q.dz;
   const float qa = __builtin_amdgcn_exp2f(-fabsf(d));
   const float T = __builtin_amdgcn_exp2f(-(y + y));
   const float E = one_minus_exp2_neg2(y, T);
   const bool ge = d >= 0.0f;
-  const float eb = ge ? q.ed : E;
+  const float eb = ge ? g.q.ed : E;
   const float qb = fmaf(-qa, eb, qa);
   const float opa = 1.0f + qa;
   const float den = fmaf(opa, qb, opa);
   const float num = ge ? E : qa * E;
-  return copysignf(num * __builtin_amdgcn_rcpf(den), z) * q.ak;
+  return copysignf(num * __builtin_amdgcn_rcpf(den), z) * g.ak;
 }
 
 template <int N>
-__device__ __forceinline__ void soft_values(const float (&w)[N], const SoftGroup& q,
+__device__ __forceinline__ void soft_values(const float (&w)[N], const SoftGroup& g,
                                             float (&out)[N]) {
-  if (q.fast) {
+  if (g.fast) {
+    float z[N], t[N], E[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) out[j] = soft_value<true>(w[j], q);
+    for (int j = 0; j < N; ++j) z[j] = (w[j] - g.mu) * g.sc;
+    exp_parts<N>(z, t, E);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const float D = fmaf(t[j], t[j] + g.q.c2, 1.0f);
+      out[j] = copysignf(E[j] * __builtin_amdgcn_rcpf(D), z[j]) * g.ak;
+    }
   } else {
 #pragma unroll
-    for (int j = 0; j < N; ++j) out[j] = soft_value<false>(w[j], q);
+    for (int j = 0; j < N; ++j) out[j] = soft_value_general(w[j], g);
   }
 }
 
-// Transition function f of Eq. 5 at x_hat (cancellation-free form).
-__device__ __forceinline__ float transition_f(float xs, float delta, float ED, const StConst& c) {
-  float x = fabsf(xs);
-  float d = x - delta;
-  float qa = __builtin_amdgcn_exp2f(-fabsf(d) * c.c2s);
-  float E = one_minus_exp_neg(x * c.s4, x * c.s4l);
-  bool ge = d >= 0.0f;
-  float eb = ge ? ED : E;
-  float qb = fmaf(-qa, eb, qa);
-  float den = (1.0f + qa) * (1.0f + qb);
-  float num = ge ? E : qa * E;
-  float F = num * __builtin_amdgcn_rcpf(den) * c.k2;
-  return copysignf(F, xs);
-}
-
-// f, f_W and f_Delta without their constant factors, in the base-2 exponent
-// domain of soft_value: with z = xs * c2s (c2s = 2 s log2 e), y = |z|,
-// dz = Delta * c2s and ed = E_Delta,
-//   f = k2 * fp,   f_W = sk4 * fwp,   f_Delta = sk4 * fdp,
-// 1/(1 + q_a) and 1/(1 + q_b) from one reciprocal of their product.  The
-// factor-gradient sums apply k2 and sk4 once per group.
-__device__ __forceinline__ void transition_parts_z(float xs, float c2s, float dz, float ed,
-                                                   float& fp, float& fwp, float& fdp) {
-  const float z = xs * c2s;
+// f, f_W and f_Delta without their constant factors in the general form:
+//   f = k2 * fp,   f_W = sk4 * fwp,   f_Delta = sk4 * fdp.
+__device__ __forceinline__ void transition_parts_general(float z, float dz, float ed, float& fp,
+                                                         float& fwp, float& fdp) {
   const float y = fabsf(z);
   const float d = y - dz;
   const float qa = __builtin_amdgcn_exp2f(-fabsf(d));
-  const float T = __builtin_amdgcn_exp2f(-(y + y));
-  const float E = one_minus_exp2_neg2(y, T);
-  const bool ge = d >= 0.0f;
-  const float eb = ge ? ed : E;
-  const float qb = fmaf(-qa, eb, qa);
-  const float opa = 1.0f + qa, opb = 1.0f + qb;
-  const float rden = __builtin_amdgcn_rcpf(opa * opb);
-  const float num = ge ? E : qa * E;
-  fp = copysignf(num * rden, xs);
-  const float ra = opb * rden, rb = opa * rden;  // 1/(1 + q_a), 1/(1 + q_b)
-  fwp = fmaf(qa * ra, ra, (qb * rb) * rb);
-  const float om = ge ? E : ed;  // 1 - q_a q_b / ... (see transition_parts)
-  fdp = copysignf((qa * eb) * om * (rden * rden), -xs);
-}
-
-// The same parts from z itself with E = 1 - 2^(-2|z|) given (the GEMM
-// epilogue forms E for a whole pass of weights, taking the series only where
-// some lane of the wave needs it), 1/(1 + q_a)^2 and 1/(1 + q_b)^2 as
-// (1 + q_b)^2 r^2 and (1 + q_a)^2 r^2 from the one reciprocal r.
-__device__ __forceinline__ void transition_parts_zE(float z, float dz, float ed, float E,
-                                                    float& fp, float& fwp, float& fdp) {
-  const float y = fabsf(z);
-  const float d = y - dz;
-  const float qa = __builtin_amdgcn_exp2f(-fabsf(d));
+  const float E = one_minus_exp2_neg2(y, __builtin_amdgcn_exp2f(-(y + y)));
   const bool ge = d >= 0.0f;
   const float eb = ge ? ed : E;
   const float qb = fmaf(-qa, eb, qa);
@@ -242,13 +255,66 @@ __device__ __forceinline__ void transition_parts_zE(float z, float dz, float ed,
   const float num = ge ? E : qa * E;
   fp = copysignf(num * rden, z);
   fwp = fmaf(qa, opb * opb, qb * (opa * opa)) * r2;
-  const float om = ge ? E : ed;
+  const float om = ge ? E : ed;  // 1 - q_a q_b
   fdp = copysignf((qa * eb) * om * r2, -z);
 }
 
-// Scales of the per-group sums of transition_parts_z: f is the hard code
-// (HARD, no scale) or k2 fp; f_W is 1 under the straight-through estimator;
-// wz turns a sum of g f_W z (z = xs c2s) into that of g f_W xs.
+// Running sums of the factor gradients of one group over its weights
+// (constant factors left out: FacScale and fac_finish below).
+struct FacSums {
+  float T, one, W, D;  // sum G f, G f_W, G f_W z, G f_Delta
+};
+
+// N weights of a group against their gradients G: z of each, the hard codes
+// where HARD; STE: f_W = 1, f_Delta = 0 (hard mode only).
+template <int N, bool HARD, bool STE>
+__device__ __forceinline__ void fac_terms(const float (&G)[N], const float (&z)[N],
+                                          const TransGroup& q, const float (&hc)[N], FacSums& s) {
+  if constexpr (STE) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      s.T = fmaf(G[j], hc[j], s.T);
+      s.one += G[j];
+      s.W = fmaf(G[j], z[j], s.W);
+    }
+  } else if (q.fast) {
+    float t[N], E[N];
+    exp_parts<N>(z, t, E);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const float D = fmaf(t[j], t[j] + q.c2, 1.0f);
+      const float r = __builtin_amdgcn_rcpf(D);
+      const float F = E[j] * r, tr = t[j] * r;
+      // (products in this order stay in range for dz up to kFastDz)
+      const float h = fmaf(4.0f, t[j], fmaf(t[j] * t[j], q.c2, q.c2));
+      const float gf = G[j] * ((h * r) * tr);
+      const float Gs = __uint_as_float(__float_as_uint(G[j]) ^ (__float_as_uint(z[j]) & 0x80000000u));
+      s.T = HARD ? fmaf(G[j], hc[j], s.T) : fmaf(Gs, F, s.T);
+      s.one += gf;
+      s.W = fmaf(gf, z[j], s.W);
+      s.D = fmaf(Gs, F * tr, s.D);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      float fp, fwp, fdp;
+      transition_parts_general(z[j], q.dz, q.ed, fp, fwp, fdp);
+      const float gf = G[j] * fwp;
+      s.T = fmaf(G[j], HARD ? hc[j] : fp, s.T);
+      s.one += gf;
+      s.W = fmaf(gf, z[j], s.W);
+      s.D = fmaf(G[j], fdp, s.D);
+    }
+  }
+}
+// A lane's sums to those of the general form (f_Delta's 2 sinh, once per lane).
+__device__ __forceinline__ void fac_finish(const TransGroup& q, FacSums& s) {
+  if (q.fast) s.D *= -q.s2;
+}
+
+// Scales of the per-group sums: f is the hard code (HARD, no scale) or k2 fp;
+// f_W is 1 under the straight-through estimator; wz turns a sum of
+// G f_W z (z = W_hat c2s) into that of G f_W W_hat.
 struct FacScale {
   float f, w, d, wz;
 };
@@ -259,27 +325,6 @@ __device__ __forceinline__ FacScale fac_scale(int mode, int ste, const StConst& 
   k.d = c.sk4;
   k.wz = k.w / c.c2s;
   return k;
-}
-
-// f, f_W and f_Delta together (backward).
-__device__ __forceinline__ void transition_parts(float xs, float delta, float ED, const StConst& c,
-                                                 float& f, float& fW, float& fD) {
-  float x = fabsf(xs);
-  float d = x - delta;
-  float qa = __builtin_amdgcn_exp2f(-fabsf(d) * c.c2s);
-  float E = one_minus_exp_neg(x * c.s4, x * c.s4l);
-  bool ge = d >= 0.0f;
-  float eb = ge ? ED : E;
-  float qb = fmaf(-qa, eb, qa);
-  float ra = __builtin_amdgcn_rcpf(1.0f + qa);
-  float rb = __builtin_amdgcn_rcpf(1.0f + qb);
-  float num = ge ? E : qa * E;
-  f = copysignf(num * ra * rb * c.k2, xs);
-  float ra2 = ra * ra, rb2 = rb * rb;
-  fW = c.sk4 * fmaf(qa, ra2, qb * rb2);
-  float om = ge ? E : ED;  // 1 - qa*qb
-  fD = copysignf(c.sk4 * (qa * eb) * om * (ra2 * rb2), -xs);
-  if (xs == 0.0f) fD = 0.0f;
 }
 
 }  // namespace catq
