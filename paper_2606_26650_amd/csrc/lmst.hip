@@ -9,15 +9,17 @@
 //   pack_ternary  2-bit storage of the codes
 //   adamw         optimizer step on a factor array
 //
-// Work split: one lane owns 8 consecutive weights (one 16-byte bf16 load), so
-// a group of g weights is g/8 adjacent lanes of one wavefront and every group
-// reduction is a butterfly over those lanes.  The kernels stream W once and
+// Work split: a lane owns octets of 8 consecutive weights (one 16-byte bf16
+// load each): one, or in the forward passes over large arrays four of a group,
+// so a group of g weights is g/8 or g/32 adjacent lanes of one wavefront and
+// every group reduction is a butterfly over those lanes.  The kernels stream W once and
 // write W_fake once: they are bound by HBM bandwidth and VALU issue, not by
 // any contraction.
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 
 #include "kernels.h"
 #include "lmst_math.h"
@@ -44,153 +46,165 @@ struct FwdArgs {
   float inv_g;
 };
 
-template <typename WT>
-__device__ __forceinline__ void group_stats_lanes(const float (&w)[8], int L, float inv_g,
+// Eq. 3 statistics of a group from the OCT octets that each of its L lanes
+// holds, in double: inside an octet (j, j+4), (j, j+2), (j, j+1), the octets of
+// a lane in order, then a butterfly over the lanes with masks L/2, ..., 1 (all
+// lanes end with the same sum).
+template <int OCT>
+__device__ __forceinline__ void group_stats_lanes(const float (&w)[OCT][8], int L, float inv_g,
                                                   float& mu0, float& alpha0) {
-  // fixed order: (j, j+4), (j, j+2), (j, j+1) inside the 8, then a butterfly
-  // over the L lanes with masks L/2, ..., 1 (all lanes end with the same sum)
-  double a[4];
+  auto total = [&](auto term) {
+    double s = 0.0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) a[j] = (double)w[j] + (double)w[j + 4];
-  double b0 = a[0] + a[2], b1 = a[1] + a[3];
-  double s = b0 + b1;
-  for (int m = L >> 1; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
-  mu0 = (float)(s * (double)inv_g);
-  double dm = (double)mu0;
+    for (int u = 0; u < OCT; ++u) {
+      double a[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) a[j] = fabs((double)w[j] - dm) + fabs((double)w[j + 4] - dm);
-  b0 = a[0] + a[2];
-  b1 = a[1] + a[3];
-  double t = b0 + b1;
-  for (int m = L >> 1; m >= 1; m >>= 1) t += __shfl_xor(t, m, 64);
-  alpha0 = (float)(t * (double)inv_g);
+      for (int j = 0; j < 4; ++j) a[j] = term(w[u][j]) + term(w[u][j + 4]);
+      const double v = (a[0] + a[2]) + (a[1] + a[3]);
+      s = u == 0 ? v : s + v;
+    }
+    for (int m = L >> 1; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
+    return s;
+  };
+  mu0 = (float)(total([](float x) { return (double)x; }) * (double)inv_g);
+  const double dm = (double)mu0;
+  alpha0 = (float)(total([dm](float x) { return fabs((double)x - dm); }) * (double)inv_g);
 }
 
-// Each thread handles FWD_U octets spaced by the grid size, so a wave keeps
-// FWD_U 16-byte loads of W (and their group scalars) in flight before it
-// computes anything; consecutive lanes still take consecutive octets, and a
-// group's lanes are always valid or invalid together (the grid size is a
-// multiple of 256 and n_oct a multiple of the lanes per group).
-constexpr int FWD_U = 4;
+// The branch of Eq. 6 on one octet o: fake weights, codes, packed word (HARD;
+// returned, 2 bits a code, code + 1 in {0, 1, 2}).
+template <typename OT, int MODE>
+__device__ __forceinline__ unsigned int fwd_octet(const FwdArgs& a, const float (&w)[8], int64_t o,
+                                                  const GroupScalars& gs, const SoftGroup& q) {
+  float out[8];
+  unsigned int word = 0;
+  if (MODE == CATQ_IDENTITY) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) out[j] = w[j];
+  } else if (MODE == CATQ_SOFT) {
+    soft_values<8>(w, q, out);
+  } else {  // HARD
+    float cs[8];
+    hard_codes8(w, gs.mu, hard_thresh(gs.delta, gs.alpha_div), cs);
+    unsigned int lo = 0, hi = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      out[j] = gs.alpha * cs[j];
+      const int c = (int)cs[j];
+      word |= (unsigned int)(c + 1) << (2 * j);
+      if (j < 4)
+        lo |= ((unsigned int)c & 0xffu) << (8 * j);
+      else
+        hi |= ((unsigned int)c & 0xffu) << (8 * (j - 4));
+    }
+    if (a.codes) {
+      uint2 v;
+      v.x = lo;
+      v.y = hi;
+      *reinterpret_cast<uint2*>(a.codes + o * 8) = v;
+    }
+  }
+  if (a.Wf) store8<OT>(reinterpret_cast<OT*>(a.Wf) + o * 8, out);
+  return word;
+}
 
+// One octet per lane: groups of fewer than 32 weights, and arrays too small
+// for the kernel below to give every SIMD a wave (see launch_fwd_mode).
 template <typename WT, typename OT, int MODE, bool STATS>
 __global__ __launch_bounds__(256) void lmst_fwd_kernel(FwdArgs a) {
-  const int64_t T = (int64_t)gridDim.x * blockDim.x;
-  const int64_t o0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (o >= a.n_oct) return;  // whole groups: all lanes of a group agree
   const int L = 1 << a.lg;
-  const int lane_in_g = (int)(o0 & (L - 1));
-  float w[FWD_U][8];
-  float st[FWD_U][2], fc[FWD_U][3];
-#pragma unroll
-  for (int u = 0; u < FWD_U; ++u) {
-    const int64_t o = o0 + u * T;
-    if (o < a.n_oct) load8<WT>(reinterpret_cast<const WT*>(a.W) + o * 8, w[u]);
-  }
-#pragma unroll
-  for (int u = 0; u < FWD_U; ++u) {
-    const int64_t o = o0 + u * T;
-    if (o >= a.n_oct) continue;
-    const int64_t grp = o >> a.lg;
-    if (!STATS) {
-      st[u][0] = a.stats[2 * grp];
-      st[u][1] = a.stats[2 * grp + 1];
+  const int64_t grp = o >> a.lg;
+  const bool first = (o & (L - 1)) == 0;
+  float w[1][8];
+  load8<WT>(reinterpret_cast<const WT*>(a.W) + o * 8, w[0]);
+  const float fm = a.dmu[grp * a.s0], fa = a.dal[grp * a.s1], fd = a.dde[grp * a.s2];
+  float mu0, alpha0;
+  if (STATS) {
+    group_stats_lanes<1>(w, L, a.inv_g, mu0, alpha0);
+    if (first) {
+      a.stats[2 * grp] = mu0;
+      a.stats[2 * grp + 1] = alpha0;
     }
-    fc[u][0] = a.dmu[grp * a.s0];
-    fc[u][1] = a.dal[grp * a.s1];
-    fc[u][2] = a.dde[grp * a.s2];
+  } else {
+    mu0 = a.stats[2 * grp];
+    alpha0 = a.stats[2 * grp + 1];
   }
-#pragma unroll
-  for (int u = 0; u < FWD_U; ++u) {
-    const int64_t o = o0 + u * T;
-    if (o >= a.n_oct) continue;  // whole groups: all lanes of a group agree
-    const int64_t grp = o >> a.lg;
-    float mu0, alpha0;
-    if (STATS) {
-      group_stats_lanes<WT>(w[u], L, a.inv_g, mu0, alpha0);
-      if (lane_in_g == 0) {
-        a.stats[2 * grp] = mu0;
-        a.stats[2 * grp + 1] = alpha0;
-      }
-    } else {
-      mu0 = st[u][0];
-      alpha0 = st[u][1];
-    }
-    GroupScalars gs = group_scalars(mu0, alpha0, fc[u][0], fc[u][1], fc[u][2], a.delta0);
-    if (a.alpha_out && lane_in_g == 0) a.alpha_out[grp] = gs.alpha;
-
-    float out[8];
-    if (MODE == CATQ_IDENTITY) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) out[j] = w[u][j];
-    } else if (MODE == CATQ_SOFT) {
-      soft_values<8>(w[u], soft_group(gs, a.st), out);
-    } else {  // HARD
-      const HardThresh th = hard_thresh(gs.delta, gs.alpha_div);
-      float cs[8];
-      hard_codes8(w[u], gs.mu, th, cs);
-      unsigned int lo = 0, hi = 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float c = cs[j];
-        out[j] = gs.alpha * c;
-        unsigned int byte = (unsigned int)(int)c & 0xffu;
-        if (j < 4)
-          lo |= byte << (8 * j);
-        else
-          hi |= byte << (8 * (j - 4));
-      }
-      if (a.codes) {
-        uint2 v;
-        v.x = lo;
-        v.y = hi;
-        *reinterpret_cast<uint2*>(a.codes + o * 8) = v;
-      }
-      if (a.packed) {
-        // element 8o + j -> bits 2j..2j+1 of the little-endian word at byte
-        // 2o: code + 1 in {0, 1, 2}
-        unsigned int word = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const unsigned int byte = j < 4 ? (lo >> (8 * j)) & 0xffu : (hi >> (8 * (j - 4))) & 0xffu;
-          word |= (unsigned int)((int)(int8_t)byte + 1) << (2 * j);
-        }
-        *reinterpret_cast<unsigned short*>(a.packed + o * 2) = (unsigned short)word;
-      }
-    }
-    if (a.Wf) store8<OT>(reinterpret_cast<OT*>(a.Wf) + o * 8, out);
-  }
+  const GroupScalars gs = group_scalars(mu0, alpha0, fm, fa, fd, a.delta0);
+  if (a.alpha_out && first) a.alpha_out[grp] = gs.alpha;
+  const unsigned int word = fwd_octet<OT, MODE>(a, w[0], o, gs, soft_group(gs, a.st));
+  if (MODE == CATQ_HARD && a.packed)
+    *reinterpret_cast<unsigned short*>(a.packed + o * 2) = (unsigned short)word;
 }
 
-// SOFT branch with cached statistics, the launch a calibration repeats every
-// soft step: one lane owns OCT octets (8 * OCT weights) of one group, so the
-// group's constants are formed once per 8 * OCT weights; a group of g weights
-// is g / (8 * OCT) adjacent lanes, and load u of lane i of a group reads octet
-// u * (g / (8 * OCT)) + i, so every load instruction of a wave covers whole
-// segments of 16 bytes per lane of a group.  Same arithmetic as
-// lmst_fwd_kernel's SOFT branch (bit-identical fake weights).
-template <typename WT, typename OT, int OCT>
-__global__ __launch_bounds__(256) void lmst_soft_kernel(FwdArgs a) {
-  constexpr int LOCT = OCT == 8 ? 3 : 2;
+// One lane owns four octets (32 weights) of one group, so the group's constants
+// and the butterflies of its statistics are paid once per 32 weights; what
+// bounds this pass is the vector ALU (float64 sums, one exponential and one
+// reciprocal per weight), not HBM: 50M bf16 weights in groups of 128 take
+// statistics + soft 57.6 -> 35.8 us (5.6 TB/s) and the packed hard codes 30.3 ->
+// 20.9 us against one octet per lane.  A group of g weights is g / 32 adjacent
+// lanes, and load u of lane i of a group reads octet u * (g / 32) + i, so every
+// load instruction of a wave covers whole segments of 16 bytes per lane of a
+// group.
+template <typename WT, typename OT, int MODE, bool STATS>
+__global__ __launch_bounds__(256) void lmst_group_kernel(FwdArgs a) {
+  constexpr int OCT = 4;
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= (a.n_oct >> LOCT)) return;
-  const int lgl = a.lg - LOCT;              // log2(lanes per group)
+  if (c >= (a.n_oct >> 2)) return;
+  const int lgl = a.lg - 2;  // log2(lanes per group)
   const int64_t grp = c >> lgl;
   const int li = (int)(c & ((1 << lgl) - 1));
-  const int64_t base = (grp << (a.lg + 3)) + 8 * (int64_t)li;   // element of octet li
-  const int64_t step = (int64_t)8 << lgl;                        // next octet of this lane
+  const int64_t base = (grp << a.lg) + li;  // the lane's octets: base + (u << lgl)
   float w[OCT][8];
 #pragma unroll
   for (int u = 0; u < OCT; ++u)
-    load8<WT>(reinterpret_cast<const WT*>(a.W) + base + u * step, w[u]);
-  const GroupScalars gs = group_scalars(a.stats[2 * grp], a.stats[2 * grp + 1], a.dmu[grp * a.s0],
-                                        a.dal[grp * a.s1], a.dde[grp * a.s2], a.delta0);
+    load8<WT>(reinterpret_cast<const WT*>(a.W) + (base + ((int64_t)u << lgl)) * 8, w[u]);
+  const float fm = a.dmu[grp * a.s0], fa = a.dal[grp * a.s1], fd = a.dde[grp * a.s2];
+  float mu0, alpha0;
+  if (STATS) {
+    group_stats_lanes<OCT>(w, 1 << lgl, a.inv_g, mu0, alpha0);
+    if (li == 0) *reinterpret_cast<float2*>(a.stats + 2 * grp) = make_float2(mu0, alpha0);
+  } else {
+    const float2 st = *reinterpret_cast<const float2*>(a.stats + 2 * grp);
+    mu0 = st.x;
+    alpha0 = st.y;
+  }
+  const GroupScalars gs = group_scalars(mu0, alpha0, fm, fa, fd, a.delta0);
   if (a.alpha_out && li == 0) a.alpha_out[grp] = gs.alpha;
   const SoftGroup q = soft_group(gs, a.st);
+  unsigned int word[OCT];
 #pragma unroll
-  for (int u = 0; u < OCT; ++u) {
-    float out[8];
-    soft_values<8>(w[u], q, out);
-    store8<OT>(reinterpret_cast<OT*>(a.Wf) + base + u * step, out);
+  for (int u = 0; u < OCT; ++u)
+    word[u] = fwd_octet<OT, MODE>(a, w[u], base + ((int64_t)u << lgl), gs, q);
+  if (MODE == CATQ_HARD && a.packed) {
+    if (lgl >= 2) {
+      // the words of a quad of lanes transposed, so that a lane stores four
+      // consecutive ones: lane i of the quad takes word i of every lane
+      const int i = li & 3;
+      const unsigned int p01 = word[0] | (word[1] << 16), p23 = word[2] | (word[3] << 16);
+      unsigned int t[4];
+      auto take = [&](auto lane_c) {
+        constexpr int k = decltype(lane_c)::value, dpp = k * 0x55;  // quad_perm [k, k, k, k]
+        const unsigned int x = (unsigned int)__builtin_amdgcn_mov_dpp((int)p01, dpp, 0xf, 0xf, true);
+        const unsigned int y = (unsigned int)__builtin_amdgcn_mov_dpp((int)p23, dpp, 0xf, 0xf, true);
+        const unsigned int v = i < 2 ? x : y;
+        t[k] = (i & 1) ? v >> 16 : v & 0xffffu;
+      };
+      take(std::integral_constant<int, 0>{});
+      take(std::integral_constant<int, 1>{});
+      take(std::integral_constant<int, 2>{});
+      take(std::integral_constant<int, 3>{});
+      uint2 v;
+      v.x = t[0] | (t[1] << 16);
+      v.y = t[2] | (t[3] << 16);
+      *reinterpret_cast<uint2*>(a.packed + 2 * (base - i + ((int64_t)i << lgl))) = v;
+    } else {
+#pragma unroll
+      for (int u = 0; u < OCT; ++u)
+        *reinterpret_cast<unsigned short*>(a.packed + 2 * (base + ((int64_t)u << lgl))) =
+            (unsigned short)word[u];
+    }
   }
 }
 
@@ -199,11 +213,18 @@ static const char* tname() {
   return sizeof(T) == 2 ? "__bf16" : "float";
 }
 
-template <typename WT, typename OT, int MODE>
-static void launch_fwd_mode(const FwdArgs& a, bool stats, dim3 grid, hipStream_t stream) {
+// The lane-per-32-weights kernel from one wave per SIMD on (1024 of them); below
+// that, one octet per lane spreads the array over four times as many waves (in
+// one-wave workgroups while there are fewer than a wave per SIMD: a 256 x 256
+// fp32 weight with statistics 7.8 -> 3.7 us against four octets per lane).
+constexpr int64_t kGroupOctets = (int64_t)1024 * 64 * 4;
+
+template <typename WT, typename OT, int MODE, bool STATS>
+static void launch_fwd_one(const FwdArgs& a, hipStream_t stream) {
+  const bool group = a.lg >= 2 && a.n_oct >= kGroupOctets;
   char tag[96];
-  std::snprintf(tag, sizeof(tag), "lmst_fwd_kernel<%s, %s, %d, %s>", tname<WT>(), tname<OT>(),
-                MODE, stats ? "true" : "false");
+  std::snprintf(tag, sizeof(tag), "lmst_%s_kernel<%s, %s, %d, %s>", group ? "group" : "fwd",
+                tname<WT>(), tname<OT>(), MODE, STATS ? "true" : "false");
   // algorithmic bytes: W read once, W_fake / codes written once, per group
   // the three factors read (or one shared value) and the stats read or written
   const double n = (double)a.n_oct * 8.0;
@@ -212,40 +233,35 @@ static void launch_fwd_mode(const FwdArgs& a, bool stats, dim3 grid, hipStream_t
   const double bytes = n * sizeof(WT) + (a.Wf ? n * sizeof(OT) : 0.0) + (a.codes ? n : 0.0) +
                        (a.packed ? n / 4.0 : 0.0) + fac + 8.0 * ng +
                        (a.alpha_out ? 4.0 * ng : 0.0);
+  const int64_t lanes = group ? a.n_oct >> 2 : a.n_oct;
+  const int nt = a.n_oct < 1024 * 64 ? 64 : 256;
+  const dim3 grid((unsigned)((lanes + nt - 1) / nt));
+  if (group)
+    CATQ_TRACED(stream, tag, 0.0, bytes, (int64_t)n, 0, 0,
+                hipLaunchKernelGGL((lmst_group_kernel<WT, OT, MODE, STATS>), grid, dim3(nt), 0,
+                                   stream, a));
+  else
+    CATQ_TRACED(stream, tag, 0.0, bytes, (int64_t)n, 0, 0,
+                hipLaunchKernelGGL((lmst_fwd_kernel<WT, OT, MODE, STATS>), grid, dim3(nt), 0, stream,
+                                   a));
+}
+
+template <typename WT, typename OT, int MODE>
+static void launch_fwd_mode(const FwdArgs& a, bool stats, hipStream_t stream) {
   if (stats)
-    CATQ_TRACED(stream, tag, 0.0, bytes, (int64_t)n, 0, 0,
-                hipLaunchKernelGGL((lmst_fwd_kernel<WT, OT, MODE, true>), grid, dim3(256), 0,
-                                   stream, a));
+    launch_fwd_one<WT, OT, MODE, true>(a, stream);
   else
-    CATQ_TRACED(stream, tag, 0.0, bytes, (int64_t)n, 0, 0,
-                hipLaunchKernelGGL((lmst_fwd_kernel<WT, OT, MODE, false>), grid, dim3(256), 0,
-                                   stream, a));
+    launch_fwd_one<WT, OT, MODE, false>(a, stream);
 }
 
 template <typename WT, typename OT>
-static void launch_fwd(const FwdArgs& a, int mode, bool stats, dim3 grid, hipStream_t stream) {
+static void launch_fwd(const FwdArgs& a, int mode, bool stats, hipStream_t stream) {
   if (mode == CATQ_IDENTITY)
-    launch_fwd_mode<WT, OT, CATQ_IDENTITY>(a, stats, grid, stream);
+    launch_fwd_mode<WT, OT, CATQ_IDENTITY>(a, stats, stream);
   else if (mode == CATQ_SOFT)
-    launch_fwd_mode<WT, OT, CATQ_SOFT>(a, stats, grid, stream);
+    launch_fwd_mode<WT, OT, CATQ_SOFT>(a, stats, stream);
   else
-    launch_fwd_mode<WT, OT, CATQ_HARD>(a, stats, grid, stream);
-}
-
-template <typename WT, typename OT>
-static void launch_soft(const FwdArgs& a, hipStream_t stream) {
-  char tag[96];
-  std::snprintf(tag, sizeof(tag), "lmst_soft_kernel<%s, %s>", tname<WT>(), tname<OT>());
-  const double n = (double)a.n_oct * 8.0;
-  const double ng = n / (8.0 * (1 << a.lg));
-  const double fac = 4.0 * ((a.s0 ? ng : 1) + (a.s1 ? ng : 1) + (a.s2 ? ng : 1));
-  const double bytes = n * sizeof(WT) + n * sizeof(OT) + fac + 8.0 * ng +
-                       (a.alpha_out ? 4.0 * ng : 0.0);
-  // 32 weights per lane (64 per lane measured slower: fewer waves in flight)
-  const int64_t lanes = a.n_oct >> 2;
-  CATQ_TRACED(stream, tag, 0.0, bytes, (int64_t)n, 0, 0,
-              hipLaunchKernelGGL((lmst_soft_kernel<WT, OT, 4>),
-                                 dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, stream, a));
+    launch_fwd_mode<WT, OT, CATQ_HARD>(a, stats, stream);
 }
 
 catq_status check_lmst_params(const catq_lmst_params* p, int64_t d_in) {
@@ -580,27 +596,14 @@ extern "C" catq_status catq_modulate_ternarize(const void* W, catq_dtype w_dtype
   a.st = make_st(p->mode == CATQ_SOFT ? (double)p->s : 1.0);
   a.inv_g = 1.0f / (float)p->group_size;
   const bool st = stats_mode == 0;
-  if (p->mode == CATQ_SOFT && !st && p->group_size >= 32) {
-    if (w_dtype == CATQ_BF16 && wf_dtype == CATQ_BF16)
-      launch_soft<bf16, bf16>(a, stream);
-    else if (w_dtype == CATQ_BF16)
-      launch_soft<bf16, float>(a, stream);
-    else if (wf_dtype == CATQ_BF16)
-      launch_soft<float, bf16>(a, stream);
-    else
-      launch_soft<float, float>(a, stream);
-    CATQ_CHECK_LAUNCH("modulate_ternarize");
-    return CATQ_OK;
-  }
-  dim3 grid((unsigned)((a.n_oct + 256 * FWD_U - 1) / (256 * FWD_U)));
   if (w_dtype == CATQ_BF16 && wf_dtype == CATQ_BF16)
-    launch_fwd<bf16, bf16>(a, p->mode, st, grid, stream);
+    launch_fwd<bf16, bf16>(a, p->mode, st, stream);
   else if (w_dtype == CATQ_BF16)
-    launch_fwd<bf16, float>(a, p->mode, st, grid, stream);
+    launch_fwd<bf16, float>(a, p->mode, st, stream);
   else if (wf_dtype == CATQ_BF16)
-    launch_fwd<float, bf16>(a, p->mode, st, grid, stream);
+    launch_fwd<float, bf16>(a, p->mode, st, stream);
   else
-    launch_fwd<float, float>(a, p->mode, st, grid, stream);
+    launch_fwd<float, float>(a, p->mode, st, stream);
   CATQ_CHECK_LAUNCH("modulate_ternarize");
   return CATQ_OK;
 }
@@ -639,12 +642,11 @@ extern "C" catq_status catq_ternarize_pack(const void* W, catq_dtype w_dtype, in
   a.delta0 = p->delta0;
   a.st = make_st(1.0);
   a.inv_g = 1.0f / (float)p->group_size;
-  dim3 grid((unsigned)((a.n_oct + 256 * FWD_U - 1) / (256 * FWD_U)));
   const bool st = stats_mode == 0;
   if (w_dtype == CATQ_BF16)
-    launch_fwd_mode<bf16, bf16, CATQ_HARD>(a, st, grid, stream);
+    launch_fwd_mode<bf16, bf16, CATQ_HARD>(a, st, stream);
   else
-    launch_fwd_mode<float, bf16, CATQ_HARD>(a, st, grid, stream);
+    launch_fwd_mode<float, bf16, CATQ_HARD>(a, st, stream);
   CATQ_CHECK_LAUNCH("ternarize_pack");
   return CATQ_OK;
 }
