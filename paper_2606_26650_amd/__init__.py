@@ -8,6 +8,8 @@ from __future__ import annotations
 
 import ctypes as C
 
+import torch
+
 from . import _lib
 from ._lib import (BF16, F32, HARD, IDENTITY, SOFT, WS_LINEAR_BWD, WS_LOSS, AttnDesc, CatqError,
                    LmstParams)
@@ -32,27 +34,32 @@ lib = _lib.load()
 
 
 def _ptr(t):
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or isinstance(t, int):
         return t
     return t.data_ptr()
 
 
+_DTYPES = {torch.bfloat16: BF16, torch.float32: F32}
+
+
 def _dt(t):
-    import torch
-    if t.dtype == torch.bfloat16:
-        return BF16
-    if t.dtype == torch.float32:
-        return F32
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    dt = _DTYPES.get(t.dtype)
+    if dt is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return dt
+
+
+# the handle of a device's current stream, without the torch.cuda.Stream object
+# that torch.cuda.current_stream() builds around it on every call
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
     if stream is not None:
         return stream
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def lmst_params(group_size=128, mode=SOFT, delta0=0.5, s=15.0, s_bwd=30.0, strides=(1, 1, 1)):

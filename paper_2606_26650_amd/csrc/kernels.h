@@ -10,6 +10,9 @@ int trace_begin(hipStream_t stream, const char* tag, double flops, double bytes,
                 int64_t N, int64_t K);
 void trace_end(int slot, hipStream_t stream);
 
+// A launch's tag, formatted only while tracing is on.
+void trace_tag(char* tag, size_t size, const char* format, ...) __attribute__((format(printf, 3, 4)));
+
 #define CATQ_TRACED(stream, tag, flops, bytes, M, N, K, launch)                   \
   do {                                                                           \
     const int slot_ = ::catq::trace_begin((stream), (tag), (flops), (bytes), (M), (N), (K)); \

@@ -223,7 +223,7 @@ template <typename WT, typename OT, int MODE, bool STATS>
 static void launch_fwd_one(const FwdArgs& a, hipStream_t stream) {
   const bool group = a.lg >= 2 && a.n_oct >= kGroupOctets;
   char tag[96];
-  std::snprintf(tag, sizeof(tag), "lmst_%s_kernel<%s, %s, %d, %s>", group ? "group" : "fwd",
+  trace_tag(tag, sizeof(tag), "lmst_%s_kernel<%s, %s, %d, %s>", group ? "group" : "fwd",
                 tname<WT>(), tname<OT>(), MODE, STATS ? "true" : "false");
   // algorithmic bytes: W read once, W_fake / codes written once, per group
   // the three factors read (or one shared value) and the stats read or written

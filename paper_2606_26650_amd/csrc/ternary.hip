@@ -509,7 +509,7 @@ catq_status launch_tern(const TernArgs& a, catq_dtype y_dtype, hipStream_t strea
                        2.0 * (double)a.M * (double)a.d_in +
                        (double)a.M * (double)a.d_out * (y_dtype == CATQ_F32 ? 4.0 : 2.0);
   static char tag[64];
-  snprintf(tag, sizeof tag, "ternary_gemv_kernel<%d, %d, %d%s>", NW, R, D, xl ? ", x in lds" : "");
+  trace_tag(tag, sizeof tag, "ternary_gemv_kernel<%d, %d, %d%s>", NW, R, D, xl ? ", x in lds" : "");
   auto launch = [&](auto vec_c, auto xl_c, auto out_c) {
     constexpr bool V = decltype(vec_c)::value, X = decltype(xl_c)::value;
     using OutT = typename decltype(out_c)::type;

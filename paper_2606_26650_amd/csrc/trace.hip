@@ -4,6 +4,8 @@
 // back on demand, so a caller can time individual kernels inside a running
 // workload without an external profiler.  Tracing is process-global and meant
 // for one host thread.
+#include <cstdarg>
+#include <cstdio>
 #include <cstring>
 #include <vector>
 
@@ -33,6 +35,15 @@ int trace_begin(hipStream_t stream, const char* tag, double flops, double bytes,
   s.rec.K = K;
   if (hipEventRecord(s.start, stream) != hipSuccess) return -1;
   return g_count++;
+}
+
+void trace_tag(char* tag, size_t size, const char* format, ...) {
+  tag[0] = '\0';
+  if (!g_on) return;
+  va_list ap;
+  va_start(ap, format);
+  std::vsnprintf(tag, size, format, ap);
+  va_end(ap);
 }
 
 void trace_end(int slot, hipStream_t stream) {
