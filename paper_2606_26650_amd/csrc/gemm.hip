@@ -1256,8 +1256,7 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
 // loop.  Within a group, lanes of half h hold k = 4h .. 4h + 3: a 16-byte load
 // of a K-contiguous row, four 4-byte loads (128-byte segments) of a K-major
 // one; product j contracts the pair k = j, 4 + j.
-// 1024 x 256 x 256: forward 35 -> 5.6 us, input gradient 37 -> 5.5 us, weight
-// gradient 116 -> 12.9 us against a 64 x 64 LDS-tiled FMA kernel; 4096 x 1024
+// 1024 x 256 x 256: forward 35 -> 5.6 us, input gradient 37 -> 5.5 us, against a 64 x 64 LDS-tiled FMA kernel; 4096 x 1024
 // x 1024: 276 -> 116 us forward (74 TF/s).  Errors against float64 halve (the
 // sums are shorter).
 template <int A_T, int B_T, int F, int NW, int U>
@@ -1368,6 +1367,67 @@ __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(GemmLaunch L) {
   }
 }
 
+// The weight gradient (both operands K-major) with too few 32 x 32 tiles: 16 x
+// 16 tiles on v_mfma_f32_16x16x4_f32, the contraction over sixteen waves as
+// above.  On 64 tiles of 32 x 32 the four waves of a SIMD take 3.4 us of products
+// one after the other (256 x 256 outputs over 1024 tokens) and three quarters of
+// the units idle: 13.1 -> 6.7 us.  Within a group of 16, lanes of quarter q hold k =
+// 4q .. 4q + 3; product j contracts k = j, 4 + j, 8 + j, 12 + j.
+template <int NW, int U>
+__global__ __launch_bounds__(NW * 64) void gemm_f32_kk16_kernel(GemmLaunch L) {
+  constexpr int T = 16;
+  __shared__ float red[NW][T][T + 1];
+  const GemmArgs& g = L.g;
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t m0 = (int64_t)(blockIdx.x / L.tiles_n) * T, n0 = (int64_t)(blockIdx.x % L.tiles_n) * T;
+  int64_t kb = 0, ke = g.K, c_off = 0;
+  if (L.ksplit > 1) {
+    kb = (int64_t)blockIdx.z * L.kchunk;
+    ke = min(g.K, kb + L.kchunk);
+    c_off = blockIdx.z * L.c_split_stride;
+  }
+  const int groups = (int)((ke - kb + 15) / 16), per = (groups + NW - 1) / NW;
+  const int g0 = min(wave * per, groups), g1 = min(g0 + per, groups);
+  // rows and columns past the matrix are clamped into it (not stored), k past
+  // the range into its last row with zero in its place
+  const float* pa = reinterpret_cast<const float*>(g.A) + min(m0 + r16, g.M - 1);
+  const float* pb = reinterpret_cast<const float*>(g.B) + min(n0 + r16, g.N - 1);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int gi = g0; gi < g1; gi += U) {
+    f32x4 a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t k = kb + 16 * (int64_t)min(gi + u, g1 - 1) + 4 * q + j, kc = min(k, ke - 1);
+        const float x = pa[kc * g.lda], y = pb[kc * g.ldb];
+        a[u][j] = k < ke ? x : 0.0f;
+        b[u][j] = k < ke ? y : 0.0f;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (gi + u >= g1) break;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][j], b[u][j], acc, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][4 * q + r][r16] = acc[r];
+  __syncthreads();
+  if (tid >= T * T) return;
+  const int64_t m = m0 + tid / T, n = n0 + tid % T;
+  if (m >= g.M || n >= g.N) return;
+  float v = 0.0f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) v += red[w][tid / T][tid % T];
+  v *= g.alpha;
+  if (g.R) v += reinterpret_cast<const float*>(g.R)[m * g.ldr + n];
+  (reinterpret_cast<float*>(g.C) + c_off)[m * g.ldc + n] = v;
+}
+
 // --------------------------------------------------------------- dispatch
 
 template <typename T>
@@ -1407,7 +1467,7 @@ static void launch_cfg(GemmLaunch& L, hipStream_t stream) {
   dim3 grid((unsigned)(L.tiles_m * L.tiles_n), 1, (unsigned)zdim);
   dim3 block(WGM * WGN * 64);
   char tag[96];
-  std::snprintf(tag, sizeof(tag), "gemm_bf16_kernel<%d, %d, %d, %d, %d, %d, %d, %s, %s, %s>", BM,
+  trace_tag(tag, sizeof(tag), "gemm_bf16_kernel<%d, %d, %d, %d, %d, %d, %d, %s, %s, %s>", BM,
                 BN, BK, WGM, WGN, A_T, B_T, tname<OutT>(), tname<RT>(), g.R ? "true" : "false");
   double flops, bytes;
   gemm_work(L, (int)sizeof(OutT), flops, bytes);
@@ -1442,7 +1502,7 @@ static void launch_dma(GemmLaunch& L, hipStream_t stream) {
   dim3 grid((unsigned)(L.tiles_m * L.tiles_n * (g.group_mode == 2 ? g.n_groups : L.ksplit)));
   dim3 block(WGM * WGN * 64);
   char tag[112];
-  std::snprintf(tag, sizeof(tag), "gemm_dma_kernel<%d, %d, %d, %d, %s%s, %s, %s, %s%s%s%s%s>", BM,
+  trace_tag(tag, sizeof(tag), "gemm_dma_kernel<%d, %d, %d, %d, %s%s, %s, %s, %s%s%s%s%s>", BM,
                 BN, WGM, WGN, AKM ? "k" : "n", BKM ? "k" : "t", tname<OutT>(), tname<RT>(),
                 g.R ? "true" : "false",
                 EPI == 1 ? ", swiglu" : (EPI == 2 ? ", swiglu_bwd" : (EPI == 3 ? ", factor_grads" : "")),
@@ -1476,7 +1536,7 @@ static void launch_few(GemmLaunch& L, hipStream_t stream) {
   L.tiles_n = (int)((g.N + BN - 1) / BN);
   const dim3 grid((unsigned)(L.tiles_m * L.tiles_n * (g.group_mode == 2 ? g.n_groups : L.ksplit)));
   char tag[96];
-  std::snprintf(tag, sizeof(tag), "gemm_few_kernel<%d, %d, %d, %s%s, %s>%s", BM, BN, S, A_T ? "k" : "n",
+  trace_tag(tag, sizeof(tag), "gemm_few_kernel<%d, %d, %d, %s%s, %s>%s", BM, BN, S, A_T ? "k" : "n",
                 B_T ? "k" : "t", tname<OutT>(), g.group_mode ? ", experts" : "");
   double flops, bytes;
   gemm_work(L, (int)sizeof(OutT), flops, bytes);
@@ -1514,12 +1574,21 @@ constexpr int64_t kF32Tiles64 = 512;
 // fp32: 64 x 64 tiles on four waves from two per compute unit on (half the
 // operand loads per product), 32 x 32 on eight waves below (on 256 x 256
 // outputs the larger tile would leave 16 workgroups); sixteen for the weight
-// gradient, whose contraction over the tokens is the longest (14.4 -> 12.9 us
-// at 1024 tokens).
+// gradient, whose contraction over the tokens is the longest, and there 16 x 16
+// while 32 x 32 would leave half the units idle (256 x 256 outputs over 1024
+// tokens: 13.1 us on 64 tiles of 32 x 32, 6.7 us on 256 of 16 x 16).
 template <int A_T, int B_T>
 static void launch_f32(GemmLaunch& L, hipStream_t stream) {
   const GemmArgs& g = L.g;
   auto tiles = [&](int64_t t) { return ((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
+  if constexpr (A_T == 1 && B_T == 1) {
+    if (tiles(32) * L.ksplit <= 128) {
+      L.tiles_n = (int)((g.N + 15) / 16);
+      hipLaunchKernelGGL((gemm_f32_kk16_kernel<16, 4>), dim3((unsigned)tiles(16), 1, (unsigned)L.ksplit),
+                         dim3(1024), 0, stream, L);
+      return;
+    }
+  }
   const bool big = tiles(64) * L.ksplit >= kF32Tiles64;
   L.tiles_n = (int)((g.N + (big ? 63 : 31)) / (big ? 64 : 32));
   const dim3 grid((unsigned)tiles(big ? 64 : 32), 1, (unsigned)L.ksplit);

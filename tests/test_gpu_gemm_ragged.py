@@ -104,6 +104,9 @@ def test_nan_row_stays_in_its_row(catq, M, N, K):
     (1021, 72, 384),    # odd token contraction over eight waves
     (2100, 136, 128),   # token contraction split in two
     (2049, 1032, 256),  # 64 x 64 tiles with remainders
+    (15, 24, 128),      # weight gradient on 16 x 16 tiles: less than one group
+    (1025, 504, 256),   # 16 x 16 tiles, one token past sixteen waves' groups
+    (1024, 520, 256),   # 32 x 32 tiles just past the 16 x 16 ones
 ])
 def test_f32_linear(catq, M, N, K):
     """The fp32 product in its three layouts (residual in the forward) against
