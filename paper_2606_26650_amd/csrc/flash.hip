@@ -483,16 +483,16 @@ __global__ __launch_bounds__(256) void flash_dsum_kernel(FaArgs a) {
 constexpr int DKDV_NT = 512;
 
 template <int D, int ROLE>  // ROLE 0: dV, 1: dK
-__device__ __forceinline__ void dkdv_waves(const FaArgs& a, uint4* sQ, uint4* sO, float* sL,
-                                           float* sD, float* sP) {
+__device__ __forceinline__ void dkdv_waves(const FaArgs& a, int bx, int kt, uint4* sQ, uint4* sO,
+                                           float* sL, float* sD, float* sP) {
   using C = fa::Cfg<D>;
   constexpr int TW = 64 * D / 8;  // 16-byte slots of one 64 x D tile
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   const int ks = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;  // key slab of this wave
-  // grid (B*Hkv*hsplit, key tiles): block chunk of a kv head takes its share
+  // bx of B*Hkv*hsplit, key tile kt: block chunk of a kv head takes its share
   // of the group's q heads and writes its own partial dK/dV
-  const int chunk = blockIdx.x % a.hsplit, bk = blockIdx.x / a.hsplit;
-  const int kt = blockIdx.y, kvh = bk % a.Hkv, b = bk / a.Hkv;
+  const int chunk = bx % a.hsplit, bk = bx / a.hsplit;
+  const int kvh = bk % a.Hkv, b = bk / a.Hkv;
   const int G = a.Hq / a.Hkv, Gc = G / a.hsplit;
   const int k0 = kt * 128;
   const int wave_first = k0 + 32 * ks;  // queries below this see none of the wave's keys
@@ -647,26 +647,24 @@ __global__ __launch_bounds__(DKDV_NT, 2) void flash_bwd_dkdv_kernel(FaArgs a) {
   __shared__ __attribute__((aligned(16))) float sL[2 * 64], sD[2 * 64];
   __shared__ __attribute__((aligned(16))) float sP[4 * 2 * 16 * 64];  // P handed from dV to dK waves
   if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < 4)
-    dkdv_waves<D, 0>(a, sQ, sO, sL, sD, sP);
+    dkdv_waves<D, 0>(a, blockIdx.x, blockIdx.y, sQ, sO, sL, sD, sP);
   else
-    dkdv_waves<D, 1>(a, sQ, sO, sL, sD, sP);
+    dkdv_waves<D, 1>(a, blockIdx.x, blockIdx.y, sQ, sO, sL, sD, sP);
 }
 
 // ------------------------------------------------------------------- dQ
 
-template <int D>
-__global__ __launch_bounds__(fa::NT, 2) void flash_bwd_dq_kernel(FaArgs a) {
+// 32 NW queries of head bh (of B*Hq), query tile qt, on NW waves of 32 queries:
+// all four waves copy both operands, or of eight the first four K, the others V.
+template <int D, int NW>
+__device__ __forceinline__ void dq_block(const FaArgs& a, int bh, int qt, uint4* sK, uint4* sV) {
   using C = fa::Cfg<D>;
   constexpr int TW = 64 * D / 8;  // 16-byte slots of one 64 x D tile
-  __shared__ uint4 sK[2][TW];
-  __shared__ uint4 sV[2][TW];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // grid (B*Hq, query tiles): the longest causal rows are dispatched first
-  const int qt = (int)gridDim.y - 1 - (int)blockIdx.y;
-  const int h = blockIdx.x % a.Hq, b = blockIdx.x / a.Hq;
+  const int h = bh % a.Hq, b = bh / a.Hq;
   const int kvh = h / (a.Hq / a.Hkv);
-  const int q0 = qt * 128;
+  const int q0 = qt * (32 * NW);
   const int qme = q0 + 32 * w + l32;
   const bf16* Qb = a.Q + ((int64_t)(b * a.Hq + h) * a.S) * D;
   const bf16* Kb = a.K + ((int64_t)(b * a.Hkv + kvh) * a.S) * D;
@@ -688,17 +686,18 @@ __global__ __launch_bounds__(fa::NT, 2) void flash_bwd_dq_kernel(FaArgs a) {
   f32x16 dq[C::DB];
 #pragma unroll
   for (int i = 0; i < C::DB; ++i) dq[i] = fa::zero16();
-  const int q_last = min(q0 + 127, a.S - 1);
+  const int q_last = min(q0 + 32 * NW - 1, a.S - 1);
   const int nkt = q_last / fa::BK + 1;
   const int wave_last = q0 + 32 * w + 31;
+  const bool rows = NW == 4 || q0 + 32 * w < a.S;   // this wave has queries
   fa::TrOffsets<D> tro;
   tro.init(lane);
   // K and V tiles of 64 keys stream into swizzled row-major LDS tiles by
   // direct copies (rows past the sequence read the last row; their P is 0);
   // K^T fragments come from transpose reads of the same K tile
   auto issue = [&](int buf, int k0) {
-    fa::dma_tile<D>(Kb, D, k0, a.S, sK[buf], w, lane);
-    fa::dma_tile<D>(Vb, D, k0, a.S, sV[buf], w, lane);
+    if (NW == 4 || w < 4) fa::dma_tile<D>(Kb, D, k0, a.S, sK + buf * TW, w, lane);
+    if (NW == 4 || w >= 4) fa::dma_tile<D>(Vb, D, k0, a.S, sV + buf * TW, w & 3, lane);
   };
   issue(0, 0);
   wait_vmem();
@@ -708,16 +707,16 @@ __global__ __launch_bounds__(fa::NT, 2) void flash_bwd_dq_kernel(FaArgs a) {
     // the next tile lands in the buffer every wave finished reading before
     // the previous barrier
     if (kt + 1 < nkt) issue(buf ^ 1, k0 + fa::BK);
-    if (k0 <= wave_last) {
+    if (rows && k0 <= wave_last) {
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb) {
         f32x16 s = fa::zero16(), dp = fa::zero16();
 #pragma unroll
         for (int t = 0; t < C::KS; ++t) {
           s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              fa::tfrag_row<D>(sK[buf], sb * 32 + l32, 2 * t + g), qf[t], s, 0, 0, 0);
+              fa::tfrag_row<D>(sK + buf * TW, sb * 32 + l32, 2 * t + g), qf[t], s, 0, 0, 0);
           dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              fa::tfrag_row<D>(sV[buf], sb * 32 + l32, 2 * t + g), of[t], dp, 0, 0, 0);
+              fa::tfrag_row<D>(sV + buf * TW, sb * 32 + l32, 2 * t + g), of[t], dp, 0, 0, 0);
         }
         // causal / length mask only where the 32 x 32 block crosses the
         // wave's diagonal or the sequence end (uniform over the wave)
@@ -742,7 +741,7 @@ __global__ __launch_bounds__(fa::NT, 2) void flash_bwd_dq_kernel(FaArgs a) {
 #pragma unroll
           for (int i = 0; i < C::DB; ++i)
             dq[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                fa::tr_read<D>(sK[buf], tro, i, 2 * sb + hh), df, dq[i], 0, 0, 0);
+                fa::tr_read<D>(sK + buf * TW, tro, i, 2 * sb + hh), df, dq[i], 0, 0, 0);
         }
       }
     }
@@ -756,6 +755,41 @@ __global__ __launch_bounds__(fa::NT, 2) void flash_bwd_dq_kernel(FaArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) dQb[i * 32 + fa::acc_row(r, g)] = dq[i][r] * a.scale;
   }
+}
+
+template <int D>
+__global__ __launch_bounds__(fa::NT, 2) void flash_bwd_dq_kernel(FaArgs a) {
+  constexpr int TW = 64 * D / 8;
+  __shared__ uint4 sK[2 * TW];
+  __shared__ uint4 sV[2 * TW];
+  // grid (B*Hq, query tiles): the longest causal rows are dispatched first
+  dq_block<D, 4>(a, blockIdx.x, (int)gridDim.y - 1 - (int)blockIdx.y, sK, sV);
+}
+
+// Both halves of the backward in one launch: dK/dV blocks of 128 keys and dQ
+// blocks of 256 queries on eight waves, independent of each other, the longest
+// of both first (two rows of key tiles, then one of query tiles).  With few
+// blocks each half is bound by its longest chain of tiles (~2.2 us each), and
+// side by side the two chains take the time of one.
+template <int D>
+__global__ __launch_bounds__(DKDV_NT, 2) void flash_bwd_kernel(FaArgs a) {
+  constexpr int TW = 64 * D / 8;
+  __shared__ uint4 sQ[2 * TW];  // Q tiles, or K tiles of a dQ block
+  __shared__ uint4 sO[2 * TW];  // dO tiles, or V tiles
+  __shared__ __attribute__((aligned(16))) float sL[2 * 64], sD[2 * 64];
+  __shared__ __attribute__((aligned(16))) float sP[4 * 2 * 16 * 64];
+  const int nkv = a.B * a.Hkv * a.hsplit, nq = a.B * a.Hq, per = 2 * nkv + nq;
+  const int p = blockIdx.x / per, i = blockIdx.x - p * per;
+  if (i >= 2 * nkv) {
+    dq_block<D, 8>(a, i - 2 * nkv, (a.S + 255) / 256 - 1 - p, sQ, sO);
+    return;
+  }
+  const int kt = 2 * p + (i >= nkv), bx = i >= nkv ? i - nkv : i;
+  if (kt * 128 >= a.S) return;
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < 4)
+    dkdv_waves<D, 0>(a, bx, kt, sQ, sO, sL, sD, sP);
+  else
+    dkdv_waves<D, 1>(a, bx, kt, sQ, sO, sL, sD, sP);
 }
 
 // ------------------------------------------------------------------ launch
@@ -788,6 +822,26 @@ catq_status flash_backward(int D, FaArgs& a, hipStream_t stream) {
                 hipLaunchKernelGGL(flash_dsum_kernel<64>, gs, dim3(256), 0, stream, a));
   CATQ_CHECK_LAUNCH("flash dsum");
   const double half = 0.5 * 2.0 * (double)a.B * a.Hq * (double)a.S * a.S * D;
+  // Both halves in one launch while its blocks are at most two and a half rounds
+  // of what the chip holds (one block per compute unit at head dimension 128, two
+  // at 64).  One launch / two (us, with D and the q/k backward): 1 x 1000 tokens,
+  // 16 heads of 128 68 / 94; 1 x 4096, 8 heads 185 / 261; 2 x 1000, 20 heads (1.9
+  // rounds) 88 / 107; 3 x 1000, 16 heads of 64 (1.1 rounds) 70 / 83; past that two
+  // launches, whose dQ blocks of four waves hold less LDS, are as fast or faster:
+  // 4 x 1000, 40 heads of 64 (3.8 rounds) 196 / 180, 3 x 2048, 16 heads of 128
+  // (4.5) 256 / 254, 2 x 4096, 40 heads (7) 1385 / 1325.
+  const int64_t blocks = (2 * (int64_t)a.B * a.Hkv * a.hsplit + (int64_t)a.B * a.Hq) * ((a.S + 255) / 256);
+  if (2 * blocks <= 5 * (D == 128 ? 256 : 512)) {
+    const dim3 g((unsigned)blocks);
+    if (D == 128)
+      CATQ_TRACED(stream, "flash_bwd_kernel<128>", 7.0 * half, 0.0, a.S, a.Hq, D,
+                  hipLaunchKernelGGL(flash_bwd_kernel<128>, g, dim3(DKDV_NT), 0, stream, a));
+    else
+      CATQ_TRACED(stream, "flash_bwd_kernel<64>", 7.0 * half, 0.0, a.S, a.Hq, D,
+                  hipLaunchKernelGGL(flash_bwd_kernel<64>, g, dim3(DKDV_NT), 0, stream, a));
+    CATQ_CHECK_LAUNCH("flash backward");
+    return CATQ_OK;
+  }
   dim3 gkv((unsigned)(a.B * a.Hkv * a.hsplit), (unsigned)((a.S + 127) / 128)), block(fa::NT);
   const dim3 block_kv(DKDV_NT);
   if (D == 128)
