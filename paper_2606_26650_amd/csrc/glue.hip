@@ -282,14 +282,39 @@ __global__ __launch_bounds__(kRankWaves * 64) void moe_rank_kernel(const int32_t
   }
 }
 
+// Rows between token order and expert order.  One block per token (and 2048
+// columns): its row is read once and written to its k slots, or its k slots'
+// rows are read four at a time (all in flight) and summed in slot order.  One
+// block per slot moved one 16-byte load per thread and latency bounded it: 3000
+// tokens x 8 slots of 2048 columns, gather 35.4 -> 19.5 us (5.6 TB/s), combine's
+// backward 35.6 -> 20.4 us, combine 30.7 -> 26.2 us.
 __global__ __launch_bounds__(256) void moe_gather_kernel(const bf16* x, const int32_t* perm,
                                                          int k, int64_t h, bf16* xg) {
-  const int64_t tj = blockIdx.x;  // token*k + slot
-  const int64_t t = tj / k;
-  const int64_t dst = perm[tj];
-  for (int64_t c = (int64_t)blockIdx.y * 256 + threadIdx.x; c < h / 8; c += (int64_t)gridDim.y * 256)
-    *reinterpret_cast<u32x4*>(xg + dst * h + c * 8) =
-        *reinterpret_cast<const u32x4*>(x + t * h + c * 8);
+  const int64_t t = blockIdx.x;
+  const int32_t* dst = perm + t * k;
+  for (int64_t c = (int64_t)blockIdx.y * 256 + threadIdx.x; c < h / 8; c += (int64_t)gridDim.y * 256) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(x + t * h + c * 8);
+    for (int s = 0; s < k; ++s)
+      *reinterpret_cast<u32x4*>(xg + (int64_t)dst[s] * h + c * 8) = v;
+  }
+}
+
+// acc += w[s] * row perm[s] (or the row itself without w) for s = 0 .. k - 1
+__device__ __forceinline__ void sum_slots(const bf16* rows, const int32_t* perm, const float* w,
+                                          int k, int64_t h, int64_t c, float (&acc)[8]) {
+  for (int s0 = 0; s0 < k; s0 += 4) {
+    float v[4][8];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      load8<bf16>(rows + (int64_t)perm[min(s0 + u, k - 1)] * h + c * 8, v[u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (s0 + u >= k) break;
+      const float ww = w ? w[s0 + u] : 1.0f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] = fmaf(ww, v[u][j], acc[j]);
+    }
+  }
 }
 
 template <typename YT>
@@ -298,20 +323,9 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(const bf16* yg, const 
                                                           int64_t h, YT* y) {
   const int64_t t = blockIdx.x;
   for (int64_t c = (int64_t)blockIdx.y * 256 + threadIdx.x; c < h / 8; c += (int64_t)gridDim.y * 256) {
-    float acc[8];
-    if (res)
-      load8<YT>(res + t * h + c * 8, acc);
-    else
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-    for (int s = 0; s < k; ++s) {
-      const int64_t r = perm[t * k + s];
-      const float ww = w[t * k + s];
-      float v[8];
-      load8<bf16>(yg + r * h + c * 8, v);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] = fmaf(ww, v[j], acc[j]);
-    }
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (res) load8<YT>(res + t * h + c * 8, acc);
+    sum_slots(yg, perm + t * k, w + t * k, k, h, c, acc);
     store8<YT>(y + t * h + c * 8, acc);
   }
 }
@@ -319,16 +333,17 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(const bf16* yg, const 
 __global__ __launch_bounds__(256) void moe_combine_bwd_kernel(const bf16* dy, const int32_t* perm,
                                                               const float* w, int k, int64_t h,
                                                               bf16* dyg) {
-  const int64_t tj = blockIdx.x;
-  const int64_t t = tj / k;
-  const int64_t r = perm[tj];
-  const float ww = w[tj];
+  const int64_t t = blockIdx.x;
   for (int64_t c = (int64_t)blockIdx.y * 256 + threadIdx.x; c < h / 8; c += (int64_t)gridDim.y * 256) {
     float v[8];
     load8<bf16>(dy + t * h + c * 8, v);
+    for (int s = 0; s < k; ++s) {
+      const float ww = w[t * k + s];
+      float o[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] *= ww;
-    store8<bf16>(dyg + r * h + c * 8, v);
+      for (int j = 0; j < 8; ++j) o[j] = v[j] * ww;
+      store8<bf16>(dyg + (int64_t)perm[t * k + s] * h + c * 8, o);
+    }
   }
 }
 
@@ -337,13 +352,7 @@ __global__ __launch_bounds__(256) void moe_scatter_add_kernel(const bf16* dxg, c
   const int64_t t = blockIdx.x;
   for (int64_t c = (int64_t)blockIdx.y * 256 + threadIdx.x; c < h / 8; c += (int64_t)gridDim.y * 256) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < k; ++s) {
-      const int64_t r = perm[t * k + s];
-      float v[8];
-      load8<bf16>(dxg + r * h + c * 8, v);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] += v[j];
-    }
+    sum_slots(dxg, perm + t * k, nullptr, k, h, c, acc);
     store8<bf16>(dx + t * h + c * 8, acc);
   }
 }
@@ -511,7 +520,7 @@ extern "C" catq_status catq_aux_moe_gather(const void* x, const int32_t* perm_ro
   CATQ_REQUIRE(count_ok(T, k, h) && h % 8 == 0, CATQ_ERR_SHAPE,
                "need T, k, h > 0, h a multiple of 8 and T*k*h <= 2^38");
   CATQ_REQUIRE(aligned16(x) && aligned16(xg), CATQ_ERR_ALIGN, "misaligned");
-  hipLaunchKernelGGL(moe_gather_kernel, dim3((unsigned)(T * k), chunks_y(h)), dim3(256), 0, stream,
+  hipLaunchKernelGGL(moe_gather_kernel, dim3((unsigned)T, chunks_y(h)), dim3(256), 0, stream,
                      (const bf16*)x, perm_row, k, h, (bf16*)xg);
   CATQ_CHECK_LAUNCH("moe gather");
   return CATQ_OK;
@@ -547,7 +556,7 @@ extern "C" catq_status catq_aux_moe_combine_bwd(const void* dy, const int32_t* p
   CATQ_REQUIRE(count_ok(T, k, h) && h % 8 == 0, CATQ_ERR_SHAPE,
                "need T, k, h > 0, h a multiple of 8 and T*k*h <= 2^38");
   CATQ_REQUIRE(aligned16(dy) && aligned16(dyg), CATQ_ERR_ALIGN, "misaligned");
-  hipLaunchKernelGGL(moe_combine_bwd_kernel, dim3((unsigned)(T * k), chunks_y(h)), dim3(256), 0,
+  hipLaunchKernelGGL(moe_combine_bwd_kernel, dim3((unsigned)T, chunks_y(h)), dim3(256), 0,
                      stream, (const bf16*)dy, perm_row, weights, k, h, (bf16*)dyg);
   CATQ_CHECK_LAUNCH("moe combine bwd");
   return CATQ_OK;

@@ -34,3 +34,33 @@ def test_routing(T, E, k):
     rows = np.empty(T * k, dtype=np.int64)
     rows[np.argsort(flat, kind="stable")] = np.arange(T * k)
     np.testing.assert_array_equal(perm.cpu().numpy().reshape(-1), rows)
+
+
+@pytest.mark.parametrize("T,k,h", [(1, 1, 8), (3, 3, 2056), (65, 4, 520), (130, 5, 4096), (7, 16, 128)])
+@pytest.mark.parametrize("y_dtype", [torch.float32, torch.bfloat16])
+def test_rows(T, k, h, y_dtype):
+    """Rows to and from expert order: slots in fours, columns in chunks of 2048."""
+    g = torch.Generator().manual_seed(T + h)
+    r = lambda *s: torch.randn(s, generator=g).to(torch.bfloat16)  # noqa: E731
+    perm = torch.randperm(T * k, generator=g).to(torch.int32).view(T, k)
+    w, x, rows, res = torch.rand((T, k), generator=g), r(T, h), r(T * k, h), r(T, h).to(y_dtype)
+    d = [t.to(DEV) for t in (perm, w, x, rows, res)]
+    xg, dyg, dx = (torch.empty(s, dtype=torch.bfloat16, device=DEV) for s in ((T * k, h), (T * k, h), (T, h)))
+    y, y0 = torch.empty((T, h), dtype=y_dtype, device=DEV), torch.empty((T, h), dtype=y_dtype, device=DEV)
+    catq.catq_aux_moe_gather(d[2], d[0], k, xg)
+    catq.catq_aux_moe_combine_bwd(d[2], d[0], d[1], dyg, k)
+    catq.catq_aux_moe_combine(d[3], d[0], d[1], d[4], y, k)
+    catq.catq_aux_moe_combine(d[3], d[0], d[1], None, y0, k)
+    catq.catq_aux_moe_scatter_add(d[3], d[0], dx, k)
+    p = perm.long().view(-1)
+    want = torch.empty_like(rows)
+    want[p] = x.repeat_interleave(k, 0)
+    assert torch.equal(xg.cpu(), want)
+    want[p] = (x.float()[:, None] * w[..., None]).to(torch.bfloat16).view(T * k, h)
+    assert torch.equal(dyg.cpu(), want)
+    sel = rows.double()[p].view(T, k, h)
+    # fp32 sums of k terms, then one rounding to the output's type
+    for got, ref in ((y, (w.double()[..., None] * sel).sum(1) + res.double()),
+                     (y0, (w.double()[..., None] * sel).sum(1)), (dx, sel.sum(1))):
+        eps = 2.0 ** -24 * (k + 1) if got.dtype == torch.float32 else 2.0 ** -8
+        assert (got.cpu().double() - ref).abs().max() <= eps * (sel.abs().sum(1) + res.double().abs()).max()
