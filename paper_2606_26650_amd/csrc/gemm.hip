@@ -1564,19 +1564,13 @@ static bool dma_ok(const GemmLaunch& L, int a_t, int b_t) {
          aligned16(g.A) && aligned16(g.B);
 }
 
-// A dense product on 256 x 256 tiles.  An unsplit forward product (both
-// operands K-contiguous) takes three B stages, its weight's copies two k
-// tiles ahead (bit-identical; in the 14B-shaped calibration step down 1.42
-// -> 1.38 ms, q|k|v 0.434 -> 0.409 ms, o 0.308 -> 0.299 ms; no loss on the
-// 1.7B-shaped block's smaller weights).
-constexpr int64_t kF32Tiles64 = 512;
-
 // fp32: 64 x 64 tiles on four waves from two per compute unit on (half the
 // operand loads per product), 32 x 32 on eight waves below (on 256 x 256
 // outputs the larger tile would leave 16 workgroups); sixteen for the weight
 // gradient, whose contraction over the tokens is the longest, and there 16 x 16
 // while 32 x 32 would leave half the units idle (256 x 256 outputs over 1024
 // tokens: 13.1 us on 64 tiles of 32 x 32, 6.7 us on 256 of 16 x 16).
+constexpr int64_t kF32Tiles64 = 512;
 template <int A_T, int B_T>
 static void launch_f32(GemmLaunch& L, hipStream_t stream) {
   const GemmArgs& g = L.g;
@@ -1599,6 +1593,11 @@ static void launch_f32(GemmLaunch& L, hipStream_t stream) {
                        stream, L);
 }
 
+// A dense product on 256 x 256 tiles.  An unsplit forward product (both
+// operands K-contiguous) takes three B stages, its weight's copies two k
+// tiles ahead (bit-identical; in the 14B-shaped calibration step down 1.42
+// -> 1.38 ms, q|k|v 0.434 -> 0.409 ms, o 0.308 -> 0.299 ms; no loss on the
+// 1.7B-shaped block's smaller weights).
 template <int A_T, int B_T, typename OutT, typename RT>
 static void launch_dense256(GemmLaunch& L, hipStream_t stream) {
   if (A_T == 0 && B_T == 0 && L.ksplit <= 1)
