@@ -105,7 +105,103 @@ __device__ __forceinline__ void hard_codes8(const float (&w)[8], float mu, const
   hard_codes_n<8>(w, mu, t, c);
 }
 
-// The transition function (Eq. 5) in the base-2 exponent domain.  With
+// The softened ternarisation of one group in the base-2 exponent domain.
+// With z = (w - mu) * sc = 2 s W_hat log2(e), y = |z| and x = |W_hat|:
+//   q_a = e^{-2 s |x - Delta|} = 2^{-|y - dz|},   e^{-4 s x} = 2^{-2 y},
+//   E = 1 - e^{-4 s x},  q_b = q_a (1 - E) (x < Delta) or q_a (1 - E_Delta),
+//   alpha f = copysign(num / ((1 + q_a)(1 + q_b)), z) * alpha / tanh(s),
+//   num = E (x >= Delta) or q_a E (x < Delta)
+// (the cancellation-free form of Eq. 5; the scalings of the exponents and of
+// the output are folded into per-group constants).
+struct SoftGroup {
+  float mu;     // mu of Eq. 3
+  float sc;     // 2 s log2(e) / alpha:  z = (w - mu) * sc
+  float inv_a;  // 1 / alpha  (when sc does not fit a float)
+  float c2s;    // 2 s log2(e)
+  float dz;     // 2 s Delta log2(e)
+  float ed;     // E_Delta = 1 - e^{-4 s Delta}
+  float ak;     // alpha / tanh(s)
+  bool fast;    // sc finite: z in one product
+};
+
+__device__ __forceinline__ SoftGroup soft_group(const GroupScalars& gs, const StConst& c) {
+  SoftGroup q;
+  q.mu = gs.mu;
+  q.inv_a = __builtin_amdgcn_rcpf(gs.alpha_div);  // 1 ulp; W_hat needs no more
+  q.c2s = c.c2s;
+  q.sc = q.inv_a * c.c2s;
+  q.fast = fabsf(q.sc) <= 3.0e38f;  // false for inf and NaN
+  q.dz = gs.delta * c.c2s;
+  q.ed = one_minus_exp_neg(gs.delta * c.s4, gs.delta * c.s4l);
+  q.ak = gs.alpha * c.k2;
+  return q;
+}
+
+// 1 - 2^{-2y} (= 1 - e^{-t}, t = 2 y ln 2) for y >= 0 given T = 2^{-2y}:
+// below t = 1/8 the series of 1 - e^{-t} to t^5 in powers of y (truncation
+// below 5e-8 relative), above it 1 - T (no cancellation: T < 0.89).
+constexpr float kSeriesY = 0.09016844f;
+__device__ __forceinline__ float one_minus_exp2_neg2(float y, float T) {
+  if (y < kSeriesY) {
+    float p = 0.04266738519f;
+    p = fmaf(p, y, -0.1538900584f);
+    p = fmaf(p, y, 0.4440328777f);
+    p = fmaf(p, y, -0.9609060287f);
+    p = fmaf(p, y, 1.386294365f);
+    return y * p;
+  }
+  return 1.0f - T;
+}
+
+// alpha * f(W_hat; s, Delta) of two weights (Eq. 5 times the group scale).
+// The series of E only where some lane of the wave has a small y; the value
+// does not depend on that branch.  One branch per two weights: per weight, as the
+// compiler places it, the pass over 352M bf16 weights with cached statistics takes
+// 276 us, per two 269 us, per eight 282 us.
+template <bool FAST>
+__device__ __forceinline__ void soft_pair(const float* w, const SoftGroup& q, float* out) {
+  float z[2], E[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    z[j] = FAST ? (w[j] - q.mu) * q.sc : ((w[j] - q.mu) * q.inv_a) * q.c2s;
+    const float y = fabsf(z[j]);
+    E[j] = 1.0f - __builtin_amdgcn_exp2f(-(y + y));
+  }
+  if (__any(fminf(fabsf(z[0]), fabsf(z[1])) < kSeriesY)) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float y = fabsf(z[j]);
+      E[j] = y < kSeriesY ? one_minus_exp2_neg2(y, 0.0f) : E[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const float d = fabsf(z[j]) - q.dz;
+    const float qa = __builtin_amdgcn_exp2f(-fabsf(d));
+    const bool ge = d >= 0.0f;
+    const float eb = ge ? q.ed : E[j];
+    const float qb = fmaf(-qa, eb, qa);
+    const float opa = 1.0f + qa;
+    const float den = fmaf(opa, qb, opa);
+    const float num = ge ? E[j] : qa * E[j];
+    out[j] = copysignf(num * __builtin_amdgcn_rcpf(den), z[j]) * q.ak;
+  }
+}
+
+template <int N>
+__device__ __forceinline__ void soft_values(const float (&w)[N], const SoftGroup& q,
+                                            float (&out)[N]) {
+  static_assert(N % 2 == 0, "pairs");
+  if (q.fast) {
+#pragma unroll
+    for (int j = 0; j < N; j += 2) soft_pair<true>(w + j, q, out + j);
+  } else {
+#pragma unroll
+    for (int j = 0; j < N; j += 2) soft_pair<false>(w + j, q, out + j);
+  }
+}
+
+// The transition function and its derivatives in the backward.  With
 // z = 2 s log2(e) W_hat, t = 2^{-|z|} = e^{-2 s |W_hat|} and dz = 2 s log2(e) Delta,
 //   E = 1 - t^2,  D = 1 + 2 cosh(2 s Delta) t + t^2,
 //   f       = copysign(E / D, z) / tanh(s)
@@ -114,10 +210,10 @@ __device__ __forceinline__ void hard_codes8(const float (&w)[8], float mu, const
 // (sinh(2u) / (cosh 2u + cosh 2d) = tanh(u - d) / 2 + tanh(u + d) / 2, and its
 // derivatives): sums of positive terms only, so no cancellation, and one
 // exponential and one reciprocal per weight.  The vector ALU is what bounds
-// the kernels that evaluate it (a form with exponentials of -|x - Delta| and
-// -2x and selects at |x| = Delta took ~12 more issue slots per weight for
-// f, ~16 for all three).  2 cosh must fit: a group with dz > kFastDz takes the
-// general form below, which has no such term.
+// the factor-gradient epilogue (the form with exponentials of -|x - Delta| and
+// -2x and selects at |x| = Delta took ~16 more issue slots per weight).
+// 2 cosh must fit: a group with dz > kFastDz takes the general form below,
+// which has no such term.
 constexpr float kFastDz = 100.0f;
 
 // 2 cosh(2 s Delta) and 2 sinh(2 s Delta) (ed = 1 - e^{-4 s Delta}); the
@@ -137,22 +233,6 @@ __device__ __forceinline__ TransGroup trans_group(float delta, const StConst& c)
   q.c2 = p + __builtin_amdgcn_rcpf(p);
   q.s2 = p * q.ed;
   return q;
-}
-
-// 1 - 2^{-2y} (= 1 - e^{-t}, t = 2 y ln 2) for y >= 0 given T = 2^{-2y}:
-// below t = 1/8 the series of 1 - e^{-t} to t^5 in powers of y (truncation
-// below 5e-8 relative), above it 1 - T (no cancellation: T < 0.89).
-constexpr float kSeriesY = 0.09016844f;
-__device__ __forceinline__ float one_minus_exp2_neg2(float y, float T) {
-  if (y < kSeriesY) {
-    float p = 0.04266738519f;
-    p = fmaf(p, y, -0.1538900584f);
-    p = fmaf(p, y, 0.4440328777f);
-    p = fmaf(p, y, -0.9609060287f);
-    p = fmaf(p, y, 1.386294365f);
-    return y * p;
-  }
-  return 1.0f - T;
 }
 
 // t = 2^{-|z|} and E = 1 - t^2 of N weights; the series only where some lane of
@@ -176,69 +256,8 @@ __device__ __forceinline__ void exp_parts(const float (&z)[N], float (&t)[N], fl
   }
 }
 
-// alpha * f(W_hat; s, Delta) of a group's weights (Eq. 5 times the scale).
-struct SoftGroup {
-  float mu;     // mu of Eq. 3
-  float sc;     // 2 s log2(e) / alpha:  z = (w - mu) * sc
-  float inv_a;  // 1 / alpha  (when sc does not fit a float)
-  float c2s;    // 2 s log2(e)
-  float ak;     // alpha / tanh(s)
-  TransGroup q;
-  bool fast;    // sc finite and 2 cosh fits
-};
-
-__device__ __forceinline__ SoftGroup soft_group(const GroupScalars& gs, const StConst& c) {
-  SoftGroup g;
-  g.mu = gs.mu;
-  g.inv_a = __builtin_amdgcn_rcpf(gs.alpha_div);  // 1 ulp; W_hat needs no more
-  g.c2s = c.c2s;
-  g.sc = g.inv_a * c.c2s;
-  g.ak = gs.alpha * c.k2;
-  g.q = trans_group(gs.delta, c);
-  g.fast = fabsf(g.sc) <= 3.0e38f && g.q.fast;  // false for inf and NaN
-  return g;
-}
-
-// The general form: with x = |W_hat|, y = |z|,
-//   q_a = e^{-2 s |x - Delta|} = 2^{-|y - dz|},  q_b = q_a (1 - E) (x < Delta) or
-//   q_a (1 - E_Delta),  f = copysign(num / ((1 + q_a)(1 + q_b)), z) / tanh(s),
-//   num = E (x >= Delta) or q_a E (x < Delta).
-__device__ __forceinline__ float soft_value_general(float w, const SoftGroup& g) {
-  const float z = ((w - g.mu) * g.inv_a) * g.c2s;
-  const float y = fabsf(z);
-  const float d = y - g.q.dz;
-  const float qa = __builtin_amdgcn_exp2f(-fabsf(d));
-  const float T = __builtin_amdgcn_exp2f(-(y + y));
-  const float E = one_minus_exp2_neg2(y, T);
-  const bool ge = d >= 0.0f;
-  const float eb = ge ? g.q.ed : E;
-  const float qb = fmaf(-qa, eb, qa);
-  const float opa = 1.0f + qa;
-  const float den = fmaf(opa, qb, opa);
-  const float num = ge ? E : qa * E;
-  return copysignf(num * __builtin_amdgcn_rcpf(den), z) * g.ak;
-}
-
-template <int N>
-__device__ __forceinline__ void soft_values(const float (&w)[N], const SoftGroup& g,
-                                            float (&out)[N]) {
-  if (g.fast) {
-    float z[N], t[N], E[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) z[j] = (w[j] - g.mu) * g.sc;
-    exp_parts<N>(z, t, E);
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      const float D = fmaf(t[j], t[j] + g.q.c2, 1.0f);
-      out[j] = copysignf(E[j] * __builtin_amdgcn_rcpf(D), z[j]) * g.ak;
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < N; ++j) out[j] = soft_value_general(w[j], g);
-  }
-}
-
-// f, f_W and f_Delta without their constant factors in the general form:
+// f, f_W and f_Delta without their constant factors in the general form (q_a,
+// q_b, E and num as in the softened ternarisation above):
 //   f = k2 * fp,   f_W = sk4 * fwp,   f_Delta = sk4 * fdp.
 __device__ __forceinline__ void transition_parts_general(float z, float dz, float ed, float& fp,
                                                          float& fwp, float& fdp) {
