@@ -1106,26 +1106,30 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
 // small layers): what bounds them is the latency of each k tile on the few
 // compute units that work (0.7 us on 128 x 128 tiles, one k tile of copies in
 // flight, against 0.2 us of products).  So this kernel spreads the output
-// over BM x BN tiles of half that size, keeps S - 1 k tiles of copies in
-// flight, and lets its four waves split each 64-deep k tile:
-// wave w multiplies the whole tile over k = 16 w .. 16 w + 15, so a fragment
-// is read from LDS by one wave only.  The four partial tiles are summed
-// through LDS in wave order.  Operand tiles, their swizzles and the bounds of
-// ragged extents are those of the kernel above.
+// over BM x BN tiles of half that size on four waves and keeps S - 1 k tiles of
+// copies in flight.  A wave owns a quarter of the tile and contracts it in the
+// order of k, as the kernel above does: an element's bits do not depend on which
+// of the two a problem's size picks.  (The waves splitting each k tile instead,
+// partial tiles summed through LDS, halve the fragment reads: the three products
+// of 512 x 4096 x 2048 take 62.9 against 63.5 us.)
+// Operand tiles, their swizzles and the bounds of ragged extents are those of
+// the kernel above.
 template <int BM, int BN, int S, bool AKM, bool BKM, typename OutT>
 __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int NW = 4, FM = BM / 32, FN = BN / 32;
+  constexpr int NW = 4;
+  static_assert(BM == 64 && BN == 64, "four waves of 32 x 32");
   using OA = std::conditional_t<AKM, DmaOpKM<BM, NW>, DmaOpNT<BM, NW, true>>;
   using OB = std::conditional_t<BKM, DmaOpKM<BN, NW>, DmaOpNT<BN, NW, true>>;
   constexpr int NI = OA::NI + OB::NI;              // copies per wave and k tile
   constexpr int STAGE = (BM + BN) * 8;             // 16-byte slots of a stage
-  constexpr int EP = BN + 8;                       // pitch of the partial tiles (floats)
-  constexpr int SLOTS = S * STAGE > NW * BM * EP / 4 ? S * STAGE : NW * BM * EP / 4;
-  __shared__ uint4 smem[SLOTS];
+  constexpr int EP = BN + 8;                       // pitch of the staged output (floats)
+  static_assert(BM * EP / 4 <= S * STAGE, "output staging");
+  __shared__ uint4 smem[S * STAGE];
   const GemmArgs& g = L.g;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = 32 * (wave >> 1), wn = 32 * (wave & 1);
   TilePlace t;
   if (!place_tile<BM>(L, lane, t)) return;
   const int64_t n0 = (int64_t)t.pn * BN;
@@ -1141,11 +1145,7 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
     oa.issue(lds0 + (uint32_t)st * (STAGE * 16), t.kb + (int64_t)kt * 64, wave);
     ob.issue(lds0 + (uint32_t)st * (STAGE * 16) + BM * 128, t.kb + (int64_t)kt * 64, wave);
   };
-  f32x16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
+  f32x16 acc{};
 #pragma unroll
   for (int q = 0; q < S - 1; ++q)
     if (q < nk) issue(q, q);
@@ -1153,14 +1153,12 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
   // Tile kt is multiplied while the fragments of tile kt + 1 are read (two
   // register sets): wait for tile kt's copies, barrier, issue the copies of
   // tile kt + S - 1, read tile kt's fragments, multiply tile kt - 1.
-  bf16x8 fa[2][FM], fb[2][FN];
+  bf16x8 fa[2][4], fb[2][4];
   auto mul = [&](auto slot_c) {
     constexpr int s = decltype(slot_c)::value;
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][i], fb[s][j], acc[i][j], 0, 0, 0);
+    for (int kk = 0; kk < 4; ++kk)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][kk], fb[s][kk], acc, 0, 0, 0);
   };
   auto step = [&](int kt, auto slot_c) {
     constexpr int s = decltype(slot_c)::value;
@@ -1179,9 +1177,10 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
     if (kt + S - 1 < nk) issue(kt + S - 1, st == 0 ? S - 1 : st - 1);
     const uint4* a = smem + st * STAGE;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) fa[s][i] = oa.frag(a, 32 * i, wave, lane);
-#pragma unroll
-    for (int j = 0; j < FN; ++j) fb[s][j] = ob.frag(a + BM * 8, 32 * j, wave, lane);
+    for (int kk = 0; kk < 4; ++kk) {
+      fa[s][kk] = oa.frag(a, wm, kk, lane);
+      fb[s][kk] = ob.frag(a + BM * 8, wn, kk, lane);
+    }
     if (kt > 0) mul(std::integral_constant<int, 1 - s>{});
     st = st + 1 == S ? 0 : st + 1;
   };
@@ -1201,13 +1200,8 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
   __syncthreads();
   float* red = reinterpret_cast<float*>(smem);
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        red[(wave * BM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * EP + 32 * j + (lane & 31)] =
-            acc[i][j][r];
+  for (int r = 0; r < 16; ++r)
+    red[(wm + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * EP + wn + (lane & 31)] = acc[r];
   __syncthreads();
   OutT* C = reinterpret_cast<OutT*>(g.C) + t.c_off;
   constexpr int LPR = BN / 4, RPP = 256 / LPR;   // lanes per row, rows per pass
@@ -1221,8 +1215,6 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
     const int64_t m = t.m0 + rr;
     if (m >= t.m_lim || n >= g.N) continue;
     f32x4 v = *reinterpret_cast<const f32x4*>(red + rr * EP + cc);
-#pragma unroll
-    for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4*>(red + (w * BM + rr) * EP + cc);
     v *= g.alpha;
     if (vec) {
       if (g.R)
