@@ -167,50 +167,65 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const bf16* gu, const b
 
 // ---------------------------------------------------------------- routing
 
-// One wavefront per token: top-k of the E logits (largest first; equal values
-// go to the lower expert id) and the softmax over the k selected logits.  PER
-// logits per lane (E <= 64 PER).
+// Logits in order as integers: a larger logit has a larger key, -0 and +0 the
+// same, a NaN the lowest of all (0).
+__device__ __forceinline__ unsigned int logit_key(float x) {
+  if (x != x) return 0u;
+  const unsigned int u = x == 0.0f ? 0u : __float_as_uint(x);
+  return (u >> 31) ? ~u : u | 0x80000000u;
+}
+__device__ __forceinline__ float key_logit(unsigned int key) {
+  if (key == 0u) return __builtin_nanf("");
+  return __uint_as_float((key >> 31) ? key & 0x7fffffffu : ~key);
+}
+
+// One wavefront per token: top-k of the E >= k logits (largest first; equal
+// values go to the lower expert id, NaN after every other) and the softmax over
+// the k selected logits.  An expert is selected once whatever the logits hold:
+// the ids index rows and experts, so they are valid and distinct also where
+// logits are NaN or -inf (then it is the weights that turn NaN or 0).  PER logits
+// per lane (E <= 64 PER).
 template <int PER>
 __global__ __launch_bounds__(256) void moe_topk_kernel(const float* logits, int64_t T, int E,
                                                        int k, int32_t* ids, float* w) {
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (t >= T) return;
-  float v[PER];
+  unsigned int key[PER];
+  unsigned int open = 0;   // bit i: expert lane + 64 i not selected yet
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int e = lane + 64 * i;
-    v[i] = e < E ? logits[t * E + e] : -INFINITY;
+    key[i] = e < E ? logit_key(logits[t * E + e]) : 0u;
+    open |= e < E ? 1u << i : 0u;
   }
   float sel = -INFINITY;   // lane j: the j-th selected logit and its expert
   int sid = 0;
   for (int j = 0; j < k; ++j) {
     // lane-local best (lowest id among equals), then across lanes
-    float bv = -INFINITY;
+    unsigned int bk = 0u;
     int be = 0x7fffffff;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = lane + 64 * i;
-      if (e < E && (v[i] > bv || (v[i] == bv && e < be))) {
-        bv = v[i];
+      if (((open >> i) & 1u) && (key[i] > bk || (key[i] == bk && e < be))) {
+        bk = key[i];
         be = e;
       }
     }
-    for (int m = 32; m >= 1; m >>= 1) {
-      const float ov = __shfl_xor(bv, m, 64);
-      const int oe = __shfl_xor(be, m, 64);
-      if (ov > bv || (ov == bv && oe < be)) {
-        bv = ov;
+    for (int mk = 32; mk >= 1; mk >>= 1) {
+      const unsigned int ok = __shfl_xor(bk, mk, 64);
+      const int oe = __shfl_xor(be, mk, 64);
+      if (ok > bk || (ok == bk && oe < be)) {
+        bk = ok;
         be = oe;
       }
     }
     if (lane == j) {
-      sel = bv;
+      sel = key_logit(bk);
       sid = be;
     }
-#pragma unroll
-    for (int i = 0; i < PER; ++i)
-      if (lane + 64 * i == be) v[i] = -INFINITY;
+    if ((be & 63) == lane) open &= ~(1u << (be >> 6));
   }
   const float ex = expf(sel - __shfl(sel, 0, 64));
   float sum = 0.f;

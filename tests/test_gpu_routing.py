@@ -64,3 +64,50 @@ def test_rows(T, k, h, y_dtype):
                      (y0, (w.double()[..., None] * sel).sum(1)), (dx, sel.sum(1))):
         eps = 2.0 ** -24 * (k + 1) if got.dtype == torch.float32 else 2.0 ** -8
         assert (got.cpu().double() - ref).abs().max() <= eps * (sel.abs().sum(1) + res.double().abs()).max()
+
+
+@pytest.mark.parametrize("E,k", [(8, 8), (8, 3), (65, 16), (300, 8)])
+def test_undefined_logits(E, k):
+    """NaN and -inf logits: every token still gets k distinct experts (NaN after
+    all others, equal ones by id) and its own rows, and only its weights and
+    outputs are undefined."""
+    T, h = 70, 72
+    g = torch.Generator().manual_seed(E)
+    logits = torch.randn((T, E), generator=g)
+    logits[3] = float("nan")
+    logits[5] = float("-inf")
+    logits[7, k - 1:] = float("nan")            # one logit fewer than slots
+    logits[8, 1:] = float("-inf")               # masked to one expert
+    logits[9, ::2] = float("nan")
+    logits[10, ::2] = float("-inf")
+    ids = torch.full((T, k), 2 ** 30, dtype=torch.int32, device=DEV)
+    perm = torch.full((T, k), 2 ** 30, dtype=torch.int32, device=DEV)
+    wts = torch.empty((T, k), device=DEV)
+    offs = torch.empty(E + 1, dtype=torch.int64, device=DEV)
+    ws = torch.empty(catq.catq_aux_moe_route_workspace_bytes(T, E, k), dtype=torch.uint8, device=DEV)
+    catq.catq_aux_moe_route(logits.to(DEV), k, ids, wts, perm, offs, ws)
+    ln = logits.numpy()
+    order = np.lexsort((np.broadcast_to(np.arange(E), (T, E)), -ln, np.isnan(ln)), axis=1)[:, :k]
+    np.testing.assert_array_equal(ids.cpu().numpy(), order)
+    flat = order.reshape(-1)
+    np.testing.assert_array_equal(offs.cpu().numpy(),
+                                  np.concatenate([[0], np.cumsum(np.bincount(flat, minlength=E))]))
+    rows = np.empty(T * k, dtype=np.int64)
+    rows[np.argsort(flat, kind="stable")] = np.arange(T * k)
+    np.testing.assert_array_equal(perm.cpu().numpy().reshape(-1), rows)
+    sel = np.take_along_axis(ln.astype(np.float64), order, 1)
+    with np.errstate(invalid="ignore"):
+        w = np.exp(sel - sel[:, :1])
+        w /= w.sum(1, keepdims=True)
+    np.testing.assert_allclose(wts.cpu().numpy(), w, rtol=2e-6)   # NaN where the reference is NaN
+    x = torch.randn((T, h), generator=g).to(torch.bfloat16)
+    xg = torch.empty((T * k, h), dtype=torch.bfloat16, device=DEV)
+    y = torch.empty((T, h), device=DEV)
+    catq.catq_aux_moe_gather(x.to(DEV), perm, k, xg)
+    catq.catq_aux_moe_combine(xg, perm, wts, None, y, k)
+    assert torch.equal(xg.cpu()[torch.from_numpy(rows)], x.repeat_interleave(k, 0))
+    undefined = np.isnan(w).any(1)
+    assert torch.isnan(y.cpu()[torch.from_numpy(undefined)]).all()
+    ok = torch.from_numpy(~undefined)
+    # fp32 weights (sum 1 within k roundings) times bf16 values
+    assert (y.cpu()[ok] - x.float()[ok]).abs().max() <= 2.0 ** -22 * (k + 1) * x.float().abs().max()
