@@ -957,7 +957,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
             if constexpr (HARD) hard_codes_n<4>(w4, mu, hard_thresh(gs.delta, gs.alpha_div), hc);
 #pragma unroll
             for (int e = 0; e < 4; ++e) z[e] = fmaf(w4[e], zk, z0);
-            fac_terms<4, HARD, STE>(v4, z, tg, hc, sum);
+            fac_terms<4, HARD, STE>(v4, z, z, tg, hc, sum);
           };
           if (F.mode == CATQ_HARD && F.ste) {
 #pragma unroll 1

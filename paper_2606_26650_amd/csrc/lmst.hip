@@ -356,19 +356,20 @@ __global__ __launch_bounds__(256) void lmst_bwd_kernel(BwdArgs a) {
   if (a.mode != CATQ_IDENTITY) {
     const float inv_a = 1.0f / gs.alpha_div;
     const TransGroup tg = trans_group(gs.delta, a.st);
-    float hc[8], z[8];
+    float hc[8], x[8], z[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       hc[j] = 0.0f;
-      z[j] = ((w[j] - gs.mu) * inv_a) * a.st.c2s;
+      x[j] = (w[j] - gs.mu) * inv_a;
+      z[j] = x[j] * a.st.c2s;
     }
     if (a.mode == CATQ_HARD) hard_codes8(w, gs.mu, hard_thresh(gs.delta, gs.alpha_div), hc);
     if (a.mode == CATQ_HARD && a.ste)
-      fac_terms<8, true, true>(G, z, tg, hc, sum);
+      fac_terms<8, true, true>(G, z, x, tg, hc, sum);
     else if (a.mode == CATQ_HARD)
-      fac_terms<8, true, false>(G, z, tg, hc, sum);
+      fac_terms<8, true, false>(G, z, x, tg, hc, sum);
     else
-      fac_terms<8, false, false>(G, z, tg, hc, sum);
+      fac_terms<8, false, false>(G, z, x, tg, hc, sum);
     fac_finish(tg, sum);
   }
   float ST = sum.T, S1 = sum.one, SW = sum.W, SD = sum.D;
@@ -382,7 +383,7 @@ __global__ __launch_bounds__(256) void lmst_bwd_kernel(BwdArgs a) {
     // the constant factors of f (k2, soft only), f_W and f_Delta (sk4)
     const FacScale k = fac_scale(a.mode, a.ste, a.st);
     S1 *= k.w;
-    SW *= k.wz;
+    SW *= k.w;
     SD *= k.d;
     ST *= k.f;
     float v[3];

@@ -281,20 +281,23 @@ __device__ __forceinline__ void transition_parts_general(float z, float dz, floa
 // Running sums of the factor gradients of one group over its weights
 // (constant factors left out: FacScale and fac_finish below).
 struct FacSums {
-  float T, one, W, D;  // sum G f, G f_W, G f_W z, G f_Delta
+  float T, one, W, D;  // sum G f, G f_W, G f_W x, G f_Delta
 };
 
-// N weights of a group against their gradients G: z of each, the hard codes
-// where HARD; STE: f_W = 1, f_Delta = 0 (hard mode only).
+// N weights of a group against their gradients G: z and x of each, the hard
+// codes where HARD; STE: f_W = 1, f_Delta = 0 (hard mode only).  x is W_hat times
+// a constant, and finite where z overflows (alpha at its lower bound): f_W is 0
+// there, and 0 times an infinite z would be NaN.
 template <int N, bool HARD, bool STE>
 __device__ __forceinline__ void fac_terms(const float (&G)[N], const float (&z)[N],
-                                          const TransGroup& q, const float (&hc)[N], FacSums& s) {
+                                          const float (&x)[N], const TransGroup& q,
+                                          const float (&hc)[N], FacSums& s) {
   if constexpr (STE) {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       s.T = fmaf(G[j], hc[j], s.T);
       s.one += G[j];
-      s.W = fmaf(G[j], z[j], s.W);
+      s.W = fmaf(G[j], x[j], s.W);
     }
   } else if (q.fast) {
     float t[N], E[N];
@@ -310,7 +313,7 @@ __device__ __forceinline__ void fac_terms(const float (&G)[N], const float (&z)[
       const float Gs = __uint_as_float(__float_as_uint(G[j]) ^ (__float_as_uint(z[j]) & 0x80000000u));
       s.T = HARD ? fmaf(G[j], hc[j], s.T) : fmaf(Gs, F, s.T);
       s.one += gf;
-      s.W = fmaf(gf, z[j], s.W);
+      s.W = fmaf(gf, x[j], s.W);
       s.D = fmaf(Gs, F * tr, s.D);
     }
   } else {
@@ -321,7 +324,7 @@ __device__ __forceinline__ void fac_terms(const float (&G)[N], const float (&z)[
       const float gf = G[j] * fwp;
       s.T = fmaf(G[j], HARD ? hc[j] : fp, s.T);
       s.one += gf;
-      s.W = fmaf(gf, z[j], s.W);
+      s.W = fmaf(gf, x[j], s.W);
       s.D = fmaf(G[j], fdp, s.D);
     }
   }

@@ -91,3 +91,52 @@ def test_constant_group_gradients(catq):
         for t in g:
             assert torch.isfinite(t).all()
             assert t[9 * K // 128].item() == 0.0
+
+
+def _grads(catq, X, dY, W, fac, mode, s, s_bwd, dw):
+    """The three factor gradients: fused (bf16, no dW_fake) or by the separate
+    kernel (fp32, or dW_fake asked for)."""
+    import torch
+    (m, k), n = X.shape, W.shape[0]
+    ng = n * k // 128
+    f = [to_dev_f32(v) for v in fac]
+    stats = torch.zeros(ng, 2, dtype=torch.float32, device="cuda")
+    wf = torch.empty_like(W)
+    p = catq.lmst_params(mode=mode, s=s, s_bwd=s_bwd)
+    catq.catq_modulate_ternarize(W, *f, p, stats, 0, W_fake=wf)
+    ws = torch.empty(catq.catq_workspace_size(0, m, n, k), dtype=torch.uint8, device="cuda")
+    g = [torch.empty(ng, dtype=torch.float32, device="cuda") for _ in range(3)]
+    catq.catq_fakeq_linear_bwd(dY, X, wf, m, n, k, W, stats, *f, p, *g, ws,
+                               dW_fake=torch.empty(n, k, dtype=torch.float32, device="cuda") if dw else None)
+    torch.cuda.synchronize()
+    return [host(t) for t in g]
+
+
+@pytest.mark.parametrize("path", ["f32", "bf16"])
+@pytest.mark.parametrize("mode,s_bwd", [(lmst.SOFT, 30.0), (lmst.HARD, 30.0), (lmst.HARD, 0.0)])
+def test_alpha_at_its_bound(catq, mode, s_bwd, path):
+    """d_alpha <= 0: alpha as a divisor is the smallest normal number and W_hat
+    up to 1e37, so f_W and f_Delta are 0 and f the sign: finite gradients."""
+    fac = [f.copy() for f in sg.perturbed_factors(47, N * K // 128)]
+    fac[1][::5] = 0.0
+    fac[1][3::5] = -0.5
+    # dY of 1e-3, so G below 0.1 and the straight-through sums G W_hat of 128
+    # weights, |W_hat| < 0.1 / 1.2e-38, below 1e38: no overflow in fp32
+    if path == "f32":
+        x, dy = sg.uniform_f32(47, "X", (M, K)), sg.uniform_f32(47, "Y", (M, N)) * np.float32(1e-3)
+        w = (sg.rng(47, "W").standard_normal((N, K)) * 0.02).astype(np.float32)
+        X, dY, W = to_dev_f32(x), to_dev_f32(dy), to_dev_f32(w)
+        x, dy, w = (t.astype(np.float64) for t in (x, dy, w))
+    else:
+        x, dy, w = sg.normal_bf16(47, "X", (M, K)), sg.normal_bf16(47, "Y", (M, N), std=1e-3), sg.normal_bf16(47, "W", (N, K), std=0.02)
+        X, dY, W = to_dev_bf16(x), to_dev_bf16(dy), to_dev_bf16(w)
+        x, dy, w = f64(x), f64(dy), f64(w)
+    ref = lmst.factor_grads(dy.T @ x, w, 128, *fac, mode, s=30.0, s_bwd=s_bwd)
+    got = _grads(catq, X, dY, W, fac, mode, 30.0, s_bwd, dw=True)
+    low = fac[1] <= 0
+    for a, b in zip(got, ref):
+        for part in (low, ~low):
+            assert np.isfinite(a[part]).all()
+            # the bounds of test_factor_gradients at s = 30; W_hat near 1e36 (the
+            # straight-through sums) adds its own rounding and that of the sums
+            assert max_norm_err(a[part], b[part]) <= 2e-5 + (4 * 30 + 1 / 900) * 2.0 ** -22
