@@ -937,7 +937,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
           const float mu = gs.mu;
           // z = (w - mu) / alpha * c2s as one FMA per weight (the scale bounded:
           // with alpha near zero, a constant group, w and mu cancel to a finite z)
-          const float zk = fminf(F.st.c2s * __builtin_amdgcn_rcpf(gs.alpha_div), 1e30f);
+          // (a comparison, not fminf: a NaN alpha stays NaN)
+          float zk = F.st.c2s * __builtin_amdgcn_rcpf(gs.alpha_div);
+          zk = zk > 1e30f ? 1e30f : zk;
           const float z0 = -mu * zk;
           const TransGroup tg = trans_group(gs.delta, F.st);
           // one pass: 4 weights (rotated into wv[0]) against 4 G values;

@@ -95,3 +95,45 @@ def test_nan_propagates_and_codes_stay_defined(catq, where):
     rows = np.arange(N) != ROW
     np.testing.assert_array_equal(bad["packed"][rows], clean["packed"][rows])
     print(f"[nan] {where}: loss {bad['loss']}, group codes all 0", flush=True)
+
+
+@pytest.mark.parametrize("mode,s_bwd", [(1, 30.0), (2, 30.0), (2, 0.0)])
+@pytest.mark.parametrize("which", ["d_mu", "d_alpha", "d_delta"])
+@pytest.mark.parametrize("dw", [False, True])
+def test_nan_factor_with_finite_dy(catq, which, mode, s_bwd, dw):
+    """A NaN factor reaches its own group's gradients on its own, not only
+    through a NaN dY, by the fused epilogue and by the separate kernel (dW_fake
+    asked for), and no other group's."""
+    import torch
+    N, K = (64, 256) if dw else (1024, 1024)    # 64 tiles of 128 x 128: the epilogue
+    W = to_dev_bf16(sg.normal_bf16(2, "W", (N, K), std=0.02))
+    X, dY = (to_dev_bf16(sg.normal_bf16(2, k, s)) for k, s in (("X", (M, K)), ("Y", (M, N))))
+    ng = N * K // G
+    fac = [np.zeros(ng), np.ones(ng), np.ones(ng)]
+    stats = torch.empty(ng, 2, device="cuda")
+    p = catq.lmst_params(mode=mode, s=15.0, s_bwd=s_bwd)
+    ws = torch.empty(catq.catq_workspace_size(0, M, N, K), dtype=torch.uint8, device="cuda")
+    out = []
+    for nan in (False, True):
+        if nan:
+            fac[["d_mu", "d_alpha", "d_delta"].index(which)][GROUP] = np.nan
+        f = [torch.from_numpy(v.astype(np.float32)).cuda() for v in fac]
+        wf = torch.empty_like(W)
+        catq.catq_modulate_ternarize(W, *f, p, stats, 0, W_fake=wf)
+        g = [torch.empty(ng, device="cuda") for _ in range(3)]
+        dwf = torch.empty(N, K, device="cuda") if dw else None
+        catq.catq_fakeq_linear_bwd(dY, X, wf, M, N, K, W, stats, *f, p, *g, ws, dW_fake=dwf)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in g])
+    # what the factor enters: mu all but a straight-through f_W = 1 and a hard
+    # code (false comparisons give 0); alpha the same and, as a factor, the
+    # d_delta gradient; Delta f and its derivatives
+    ste = mode == 2 and s_bwd == 0.0
+    nan = {"d_mu": (not ste, True, not ste), "d_alpha": (not ste, True, True),
+           "d_delta": (not ste, not ste, not ste)}[which]
+    for i, (a, b) in enumerate(zip(*out)):
+        assert np.isfinite(a).all()
+        if nan[i]:
+            assert np.isnan(b[GROUP])
+        keep = np.arange(ng) != GROUP
+        np.testing.assert_array_equal(a[keep], b[keep])
