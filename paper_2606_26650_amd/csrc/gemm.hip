@@ -935,18 +935,22 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
         FacSums sum = {0.f, 0.f, 0.f, 0.f};
         if (mrow + rr < m_lim && F.mode != CATQ_IDENTITY) {
           const float mu = gs.mu;
-          // z = (w - mu) / alpha * c2s as one FMA per weight (the scale bounded:
-          // with alpha near zero, a constant group, w and mu cancel to a finite z)
-          // (a comparison, not fminf: a NaN alpha stays NaN)
-          float zk = F.st.c2s * __builtin_amdgcn_rcpf(gs.alpha_div);
-          zk = zk > 1e30f ? 1e30f : zk;
-          const float z0 = -mu * zk;
+          // z = (w - mu) / alpha * c2s as one FMA per weight (straight through:
+          // W_hat, no transition to evaluate); where the scale is beyond 1e20,
+          // with alpha near zero, or NaN, in steps from the exact w - mu
+          const float cs = F.ste ? 1.0f : F.st.c2s;
+          const float inv_a = __builtin_amdgcn_rcpf(gs.alpha_div);
+          const float zk = inv_a * cs, z0 = -mu * zk;
+          const bool plain = zk <= 1e20f;
           const TransGroup tg = trans_group(gs.delta, F.st);
           // one pass: 4 weights (rotated into wv[0]) against 4 G values;
           // (HARD, STE: the straight-through estimator, hard mode only) are
-          // launch constants, one loop per combination
-          auto pass = [&](int q, auto hard_c, auto ste_c) {
+          // launch constants, one loop per combination, and one for the waves
+          // with a row whose scale is not PLAIN (a test in the loop made the
+          // routed experts' launches 2% slower)
+          auto pass = [&](int q, auto hard_c, auto ste_c, auto plain_c) {
             constexpr bool HARD = decltype(hard_c)::value, STE = decltype(ste_c)::value;
+            constexpr bool PLAIN = decltype(plain_c)::value;
             const f32x4 v = *reinterpret_cast<const f32x4*>(st + rr * EP + cq + 4 * q);
             const f32x4 w = widen4(wv[0]);
             // the next pass's weights into wv[0] (registers rotated: no
@@ -959,18 +963,31 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
             if constexpr (HARD) hard_codes_n<4>(w4, mu, hard_thresh(gs.delta, gs.alpha_div), hc);
 #pragma unroll
             for (int e = 0; e < 4; ++e) z[e] = fmaf(w4[e], zk, z0);
+            if (!PLAIN && !plain) {
+              // beyond 1e30 f is saturated and f_W is 0: any finite z will do
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                z[e] = ((w4[e] - mu) * inv_a) * cs;
+                if (!STE && fabsf(z[e]) > 1e30f) z[e] = copysignf(1e30f, z[e]);
+              }
+            }
             fac_terms<4, HARD, STE>(v4, z, z, tg, hc, sum);
           };
-          if (F.mode == CATQ_HARD && F.ste) {
+          auto passes = [&](auto hard_c, auto ste_c) {
+            if (__all(plain)) {
 #pragma unroll 1
-            for (int q = 0; q < 4; ++q) pass(q, std::true_type{}, std::true_type{});
-          } else if (F.mode == CATQ_HARD) {
+              for (int q = 0; q < 4; ++q) pass(q, hard_c, ste_c, std::true_type{});
+            } else {
 #pragma unroll 1
-            for (int q = 0; q < 4; ++q) pass(q, std::true_type{}, std::false_type{});
-          } else {
-#pragma unroll 1
-            for (int q = 0; q < 4; ++q) pass(q, std::false_type{}, std::false_type{});
-          }
+              for (int q = 0; q < 4; ++q) pass(q, hard_c, ste_c, std::false_type{});
+            }
+          };
+          if (F.mode == CATQ_HARD && F.ste)
+            passes(std::true_type{}, std::true_type{});
+          else if (F.mode == CATQ_HARD)
+            passes(std::true_type{}, std::false_type{});
+          else
+            passes(std::false_type{}, std::false_type{});
           fac_finish(tg, sum);
         }
         float sT = sum.T, s1 = sum.one, sW = sum.W, sD = sum.D;

@@ -336,7 +336,7 @@ __device__ __forceinline__ void fac_finish(const TransGroup& q, FacSums& s) {
 
 // Scales of the per-group sums: f is the hard code (HARD, no scale) or k2 fp;
 // f_W is 1 under the straight-through estimator; wz turns a sum of
-// G f_W z (z = W_hat c2s) into that of G f_W W_hat.
+// G f_W z (z = W_hat c2s, or W_hat straight through) into that of G f_W W_hat.
 struct FacScale {
   float f, w, d, wz;
 };
@@ -345,7 +345,7 @@ __device__ __forceinline__ FacScale fac_scale(int mode, int ste, const StConst& 
   k.f = (mode == CATQ_SOFT) ? c.k2 : 1.0f;
   k.w = ste ? 1.0f : c.sk4;
   k.d = c.sk4;
-  k.wz = k.w / c.c2s;
+  k.wz = ste ? 1.0f : c.sk4 / c.c2s;
   return k;
 }
 

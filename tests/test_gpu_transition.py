@@ -140,3 +140,29 @@ def test_alpha_at_its_bound(catq, mode, s_bwd, path):
             # the bounds of test_factor_gradients at s = 30; W_hat near 1e36 (the
             # straight-through sums) adds its own rounding and that of the sums
             assert max_norm_err(a[part], b[part]) <= 2e-5 + (4 * 30 + 1 / 900) * 2.0 ** -22
+
+
+@pytest.mark.parametrize("mode,s_bwd", [(lmst.SOFT, 30.0), (lmst.HARD, 30.0), (lmst.HARD, 0.0)])
+def test_tiny_alpha_fused(catq, mode, s_bwd):
+    """Groups of weights of 1e-31 and 1e-22 (2 s log2(e) / alpha beyond any bound
+    on it that keeps constant groups finite) and groups with d_alpha <= 0, in the
+    factor epilogue."""
+    n, k = 1024, 1024    # 64 tiles of 128 x 128
+    rng = sg.rng(48, "W")
+    w = rng.standard_normal((n, k)) * 0.02
+    for i, scale in enumerate((1e-31, 1e-22)):
+        w[i::9, :256] *= scale / 0.02
+    wb = sg.f32_to_bf16_bits(w.astype(np.float32))
+    xb, dyb = sg.normal_bf16(48, "X", (M, k)), sg.normal_bf16(48, "Y", (M, n), std=1e-3)
+    fac = [f.copy() for f in sg.perturbed_factors(48, n * k // 128)]
+    low = np.zeros((n, k // 128), bool)
+    low[4::9, :2] = True
+    fac[1][low.reshape(-1)] = -0.25
+    ref = lmst.factor_grads(f64(dyb).T @ f64(xb), f64(wb), 128, *fac, mode, s=30.0, s_bwd=s_bwd)
+    got = _grads(catq, to_dev_bf16(xb), to_dev_bf16(dyb), to_dev_bf16(wb), fac, mode, 30.0, s_bwd, dw=False)
+    for a, b in zip(got, ref):
+        a, b = a.reshape(n, -1), b.reshape(n, -1)
+        for r in range(9):
+            # (the bounds of test_factor_gradients at s = 30)
+            assert np.isfinite(a[r::9]).all()
+            assert max_norm_err(a[r::9, :2], b[r::9, :2]) <= 2e-5 + (4 * 30 + 1 / 900) * 2.0 ** -22, r
