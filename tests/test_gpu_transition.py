@@ -166,3 +166,23 @@ def test_tiny_alpha_fused(catq, mode, s_bwd):
             # (the bounds of test_factor_gradients at s = 30)
             assert np.isfinite(a[r::9]).all()
             assert max_norm_err(a[r::9, :2], b[r::9, :2]) <= 2e-5 + (4 * 30 + 1 / 900) * 2.0 ** -22, r
+
+
+@pytest.mark.parametrize("dy_std", [1e-3, 1e-14, 1e-24])
+@pytest.mark.parametrize("s", [15.0, 44.3, 44.5, 69.2, 100.0])  # dz 21.6, 63.9, 64.2, 99.8, 144 at Delta = 0.5
+@pytest.mark.parametrize("mode", [lmst.SOFT, lmst.HARD])
+@pytest.mark.parametrize("fused", [False, True])
+def test_gradient_scale(catq, mode, s, dy_std, fused):
+    """Gradients of any size keep their digits: G of 1e-2 down to 1e-23, with
+    sharpnesses on both sides of the line between the two forms (and of an
+    earlier one at dz = 100)."""
+    n, k = (1024, 1024) if fused else (N, K)
+    xb, dyb = sg.normal_bf16(49, "X", (M, k)), sg.normal_bf16(49, "Y", (M, n), std=dy_std)
+    wb = sg.normal_bf16(49, "W", (n, k), std=0.02)
+    ng = n * k // 128
+    fac = list(sg.perturbed_factors(49, ng))
+    fac[2] = np.ones(ng, np.float32)
+    ref = lmst.factor_grads(f64(dyb).T @ f64(xb), f64(wb), 128, *fac, mode, s=s, s_bwd=s)
+    got = _grads(catq, to_dev_bf16(xb), to_dev_bf16(dyb), to_dev_bf16(wb), fac, mode, s, s, dw=not fused)
+    for a, b in zip(got, ref):
+        assert max_norm_err(a, b) <= 2e-5 + (4 * s + 1 / s ** 2) * 2.0 ** -22   # as test_factor_gradients
