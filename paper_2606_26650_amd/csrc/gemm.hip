@@ -988,6 +988,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
             passes(std::true_type{}, std::false_type{});
           else
             passes(std::false_type{}, std::false_type{});
+          fac_finish(tg, sum);
         }
         float sT = sum.T, s1 = sum.one, sW = sum.W, sD = sum.D;
 #pragma unroll

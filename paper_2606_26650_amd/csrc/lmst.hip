@@ -370,6 +370,7 @@ __global__ __launch_bounds__(256) void lmst_bwd_kernel(BwdArgs a) {
       fac_terms<8, true, false>(G, z, x, tg, hc, sum);
     else
       fac_terms<8, false, false>(G, z, x, tg, hc, sum);
+    fac_finish(tg, sum);
   }
   float ST = sum.T, S1 = sum.one, SW = sum.W, SD = sum.D;
   for (int m = L >> 1; m >= 1; m >>= 1) {

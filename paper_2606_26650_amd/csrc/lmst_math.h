@@ -212,18 +212,21 @@ __device__ __forceinline__ void soft_values(const float (&w)[N], const SoftGroup
 // exponential and one reciprocal per weight.  The vector ALU is what bounds
 // the factor-gradient epilogue (the form with exponentials of -|x - Delta| and
 // -2x and selects at |x| = Delta took ~16 more issue slots per weight).
-// 2 cosh must fit, and 2^{-|z|} of weights past the threshold must not fall
-// below the normal range while it still counts: from dz = 64 on (s = 44 at
-// Delta = 0.5; the paper's schedule ends at 43.3) a group takes the general form
-// below.  At 64 the weights that lose digits are those with f_W and f_Delta
-// below 2^-62 of their peak.
-constexpr float kFastDz = 64.0f;
+// 2 sinh is applied to a lane's sum of f_Delta, whose terms are 2^-dz of its
+// size until then, and 2^{-|z|} of weights past the threshold must not fall below
+// the normal range while it still counts: beyond dz = 60 (the paper's schedule ends
+// at dz = 43.3 for d_Delta = 1) a group takes the general form below.  At 60 the
+// terms keep all their digits for gradients G from 2^-64 (5e-20) up, and the
+// weights that lose some have f_W and f_Delta below 2^-66 of their peak.
+// (2 sinh per weight instead, without that limit on G: the routed experts'
+// launches 3-8% slower, by another register or a longer chain in the loop.)
+constexpr float kFastDz = 60.0f;
 
-// 2 cosh(2 s Delta) and -2 sinh(2 s Delta) (ed = 1 - e^{-4 s Delta}); the
+// 2 cosh(2 s Delta) and 2 sinh(2 s Delta) (ed = 1 - e^{-4 s Delta}); the
 // exponent is formed in float64, so that its rounding (2^-24 of ~50) does not
 // enter f, whose dead zone is proportional to 1 / cosh.
 struct TransGroup {
-  float dz, ed, c2, ns2;
+  float dz, ed, c2, s2;
   bool fast;
 };
 __device__ __forceinline__ TransGroup trans_group(float delta, const StConst& c) {
@@ -234,7 +237,7 @@ __device__ __forceinline__ TransGroup trans_group(float delta, const StConst& c)
   q.fast = fabsf(q.dz) <= kFastDz;  // false for NaN
   const float p = ldexpf(__builtin_amdgcn_exp2f((float)(e - n)), q.fast ? (int)n : 0);
   q.c2 = p + __builtin_amdgcn_rcpf(p);
-  q.ns2 = -p * q.ed;
+  q.s2 = p * q.ed;
   return q;
 }
 
@@ -282,7 +285,7 @@ __device__ __forceinline__ void transition_parts_general(float z, float dz, floa
 }
 
 // Running sums of the factor gradients of one group over its weights
-// (constant factors left out: FacScale below).
+// (constant factors left out: FacScale and fac_finish below).
 struct FacSums {
   float T, one, W, D;  // sum G f, G f_W, G f_W x, G f_Delta
 };
@@ -307,18 +310,17 @@ __device__ __forceinline__ void fac_terms(const float (&G)[N], const float (&z)[
     exp_parts<N>(z, t, E);
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      const float D = fmaf(t[j], t[j] + q.c2, 1.0f);
-      const float r = __builtin_amdgcn_rcpf(D);
+      const float u = fmaf(t[j], t[j], 1.0f);
+      const float r = __builtin_amdgcn_rcpf(fmaf(q.c2, t[j], u));
       const float F = E[j] * r, tr = t[j] * r;
-      // (in this order every product stays in range for dz up to kFastDz, whatever
-      // the scale of G: 2 cosh and 2 sinh meet t / D before G comes in)
-      const float h = fmaf(4.0f, t[j], fmaf(t[j] * t[j], q.c2, q.c2));
+      // (products in this order stay in range for dz up to kFastDz)
+      const float h = fmaf(4.0f, t[j], q.c2 * u);
       const float gf = G[j] * ((h * r) * tr);
       const float Gs = __uint_as_float(__float_as_uint(G[j]) ^ (__float_as_uint(z[j]) & 0x80000000u));
       s.T = HARD ? fmaf(G[j], hc[j], s.T) : fmaf(Gs, F, s.T);
       s.one += gf;
       s.W = fmaf(gf, x[j], s.W);
-      s.D = fmaf(Gs, F * (tr * q.ns2), s.D);
+      s.D = fmaf(Gs, F * tr, s.D);
     }
   } else {
 #pragma unroll
@@ -333,6 +335,11 @@ __device__ __forceinline__ void fac_terms(const float (&G)[N], const float (&z)[
     }
   }
 }
+// A lane's sums to those of the general form (f_Delta's 2 sinh, once per lane).
+__device__ __forceinline__ void fac_finish(const TransGroup& q, FacSums& s) {
+  if (q.fast) s.D *= -q.s2;
+}
+
 // Scales of the per-group sums: f is the hard code (HARD, no scale) or k2 fp;
 // f_W is 1 under the straight-through estimator; wz turns a sum of
 // G f_W z (z = W_hat c2s, or W_hat straight through) into that of G f_W W_hat.
