@@ -72,8 +72,11 @@ __device__ __forceinline__ void group_stats_lanes(const float (&w)[OCT][8], int 
 }
 
 // The branch of Eq. 6 on one octet o: fake weights, codes, packed word (HARD;
-// returned, 2 bits a code, code + 1 in {0, 1, 2}).
-template <typename OT, int MODE>
+// returned, 2 bits a code, code + 1 in {0, 1, 2}).  FAKE: the fake weights are
+// the one output.  A test of each pointer between a lane's octets keeps their
+// arithmetic from interleaving: 352M bf16 weights with cached statistics take
+// 306 us soft with it, 265 us without (5.5 TB/s), and 284 us hard, 248 us without.
+template <typename OT, int MODE, bool FAKE>
 __device__ __forceinline__ unsigned int fwd_octet(const FwdArgs& a, const float (&w)[8], int64_t o,
                                                   const GroupScalars& gs, const SoftGroup& q) {
   float out[8];
@@ -97,20 +100,20 @@ __device__ __forceinline__ unsigned int fwd_octet(const FwdArgs& a, const float 
       else
         hi |= ((unsigned int)c & 0xffu) << (8 * (j - 4));
     }
-    if (a.codes) {
+    if (!FAKE && a.codes) {
       uint2 v;
       v.x = lo;
       v.y = hi;
       *reinterpret_cast<uint2*>(a.codes + o * 8) = v;
     }
   }
-  if (a.Wf) store8<OT>(reinterpret_cast<OT*>(a.Wf) + o * 8, out);
+  if (FAKE || a.Wf) store8<OT>(reinterpret_cast<OT*>(a.Wf) + o * 8, out);
   return word;
 }
 
 // One octet per lane: groups of fewer than 32 weights, and arrays too small
-// for the kernel below to give every SIMD a wave (see launch_fwd_mode).
-template <typename WT, typename OT, int MODE, bool STATS>
+// for the kernel below to give every SIMD a wave (see launch_fwd_one).
+template <typename WT, typename OT, int MODE, bool STATS, bool FAKE>
 __global__ __launch_bounds__(256) void lmst_fwd_kernel(FwdArgs a) {
   const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (o >= a.n_oct) return;  // whole groups: all lanes of a group agree
@@ -133,21 +136,21 @@ __global__ __launch_bounds__(256) void lmst_fwd_kernel(FwdArgs a) {
   }
   const GroupScalars gs = group_scalars(mu0, alpha0, fm, fa, fd, a.delta0);
   if (a.alpha_out && first) a.alpha_out[grp] = gs.alpha;
-  const unsigned int word = fwd_octet<OT, MODE>(a, w[0], o, gs, soft_group(gs, a.st));
-  if (MODE == CATQ_HARD && a.packed)
+  const unsigned int word = fwd_octet<OT, MODE, FAKE>(a, w[0], o, gs, soft_group(gs, a.st));
+  if (!FAKE && a.packed)
     *reinterpret_cast<unsigned short*>(a.packed + o * 2) = (unsigned short)word;
 }
 
 // One lane owns four octets (32 weights) of one group, so the group's constants
 // and the butterflies of its statistics are paid once per 32 weights; what
-// bounds this pass is the vector ALU (float64 sums, one exponential and one
+// bounds this pass is the vector ALU (float64 sums, two exponentials and one
 // reciprocal per weight), not HBM: 50M bf16 weights in groups of 128 take
-// statistics + soft 57.6 -> 35.8 us (5.6 TB/s) and the packed hard codes 30.3 ->
-// 20.9 us against one octet per lane.  A group of g weights is g / 32 adjacent
+// statistics + soft 59 -> 40.7 us (5.1 TB/s) and the packed hard codes 29 ->
+// 21.0 us against four octets of different groups per lane.  A group of g weights is g / 32 adjacent
 // lanes, and load u of lane i of a group reads octet u * (g / 32) + i, so every
 // load instruction of a wave covers whole segments of 16 bytes per lane of a
 // group.
-template <typename WT, typename OT, int MODE, bool STATS>
+template <typename WT, typename OT, int MODE, bool STATS, bool FAKE>
 __global__ __launch_bounds__(256) void lmst_group_kernel(FwdArgs a) {
   constexpr int OCT = 4;
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -176,8 +179,8 @@ __global__ __launch_bounds__(256) void lmst_group_kernel(FwdArgs a) {
   unsigned int word[OCT];
 #pragma unroll
   for (int u = 0; u < OCT; ++u)
-    word[u] = fwd_octet<OT, MODE>(a, w[u], base + ((int64_t)u << lgl), gs, q);
-  if (MODE == CATQ_HARD && a.packed) {
+    word[u] = fwd_octet<OT, MODE, FAKE>(a, w[u], base + ((int64_t)u << lgl), gs, q);
+  if (!FAKE && a.packed) {
     if (lgl >= 2) {
       // the words of a quad of lanes transposed, so that a lane stores four
       // consecutive ones: lane i of the quad takes word i of every lane
@@ -219,7 +222,7 @@ static const char* tname() {
 // fp32 weight with statistics 7.8 -> 3.7 us against four octets per lane).
 constexpr int64_t kGroupOctets = (int64_t)1024 * 64 * 4;
 
-template <typename WT, typename OT, int MODE, bool STATS>
+template <typename WT, typename OT, int MODE, bool STATS, bool FAKE>
 static void launch_fwd_one(const FwdArgs& a, hipStream_t stream) {
   const bool group = a.lg >= 2 && a.n_oct >= kGroupOctets;
   char tag[96];
@@ -238,20 +241,31 @@ static void launch_fwd_one(const FwdArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)((lanes + nt - 1) / nt));
   if (group)
     CATQ_TRACED(stream, tag, 0.0, bytes, (int64_t)n, 0, 0,
-                hipLaunchKernelGGL((lmst_group_kernel<WT, OT, MODE, STATS>), grid, dim3(nt), 0,
+                hipLaunchKernelGGL((lmst_group_kernel<WT, OT, MODE, STATS, FAKE>), grid, dim3(nt), 0,
                                    stream, a));
   else
     CATQ_TRACED(stream, tag, 0.0, bytes, (int64_t)n, 0, 0,
-                hipLaunchKernelGGL((lmst_fwd_kernel<WT, OT, MODE, STATS>), grid, dim3(nt), 0, stream,
+                hipLaunchKernelGGL((lmst_fwd_kernel<WT, OT, MODE, STATS, FAKE>), grid, dim3(nt), 0, stream,
                                    a));
 }
 
 template <typename WT, typename OT, int MODE>
 static void launch_fwd_mode(const FwdArgs& a, bool stats, hipStream_t stream) {
+  // (codes and packed words come in the hard branch only, W_fake always in the
+  // others)
+  if constexpr (MODE == CATQ_HARD) {
+    if (a.Wf == nullptr || a.codes != nullptr || a.packed != nullptr) {
+      if (stats)
+        launch_fwd_one<WT, OT, MODE, true, false>(a, stream);
+      else
+        launch_fwd_one<WT, OT, MODE, false, false>(a, stream);
+      return;
+    }
+  }
   if (stats)
-    launch_fwd_one<WT, OT, MODE, true>(a, stream);
+    launch_fwd_one<WT, OT, MODE, true, true>(a, stream);
   else
-    launch_fwd_one<WT, OT, MODE, false>(a, stream);
+    launch_fwd_one<WT, OT, MODE, false, true>(a, stream);
 }
 
 template <typename WT, typename OT>
