@@ -15,6 +15,7 @@
 // every group reduction is a butterfly over those lanes.  The kernels stream W once and
 // write W_fake once: they are bound by HBM bandwidth and VALU issue, not by
 // any contraction.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -112,7 +113,7 @@ __device__ __forceinline__ unsigned int fwd_octet(const FwdArgs& a, const float 
 }
 
 // One octet per lane: groups of fewer than 32 weights, and arrays too small
-// for the kernel below to give every SIMD a wave (see launch_fwd_one).
+// for the kernel below to give every SIMD a wave (see launch_fwd_chunk).
 template <typename WT, typename OT, int MODE, bool STATS, bool FAKE>
 __global__ __launch_bounds__(256) void lmst_fwd_kernel(FwdArgs a) {
   const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -223,7 +224,7 @@ static const char* tname() {
 constexpr int64_t kGroupOctets = (int64_t)1024 * 64 * 4;
 
 template <typename WT, typename OT, int MODE, bool STATS, bool FAKE>
-static void launch_fwd_one(const FwdArgs& a, hipStream_t stream) {
+static void launch_fwd_chunk(const FwdArgs& a, hipStream_t stream) {
   const bool group = a.lg >= 2 && a.n_oct >= kGroupOctets;
   char tag[96];
   trace_tag(tag, sizeof(tag), "lmst_%s_kernel<%s, %s, %d, %s>", group ? "group" : "fwd",
@@ -247,6 +248,28 @@ static void launch_fwd_one(const FwdArgs& a, hipStream_t stream) {
     CATQ_TRACED(stream, tag, 0.0, bytes, (int64_t)n, 0, 0,
                 hipLaunchKernelGGL((lmst_fwd_kernel<WT, OT, MODE, STATS, FAKE>), grid, dim3(nt), 0, stream,
                                    a));
+}
+
+// A launch has fewer than 2^32 lanes (the grid is silently taken modulo that), so
+// arrays of more octets go in several: groups of 16 from 2^34 weights on.
+template <typename WT, typename OT, int MODE, bool STATS, bool FAKE>
+static void launch_fwd_one(const FwdArgs& a, hipStream_t stream) {
+  constexpr int64_t kChunk = (int64_t)1 << 31;   // octets, whole groups
+  for (int64_t o = 0; o < a.n_oct; o += kChunk) {
+    FwdArgs c = a;
+    const int64_t g = o >> a.lg;
+    c.n_oct = std::min(a.n_oct - o, kChunk);
+    c.W = reinterpret_cast<const WT*>(a.W) + o * 8;
+    c.dmu += g * a.s0;
+    c.dal += g * a.s1;
+    c.dde += g * a.s2;
+    c.stats += 2 * g;
+    if (a.Wf) c.Wf = reinterpret_cast<OT*>(a.Wf) + o * 8;
+    if (a.codes) c.codes += o * 8;
+    if (a.packed) c.packed += o * 2;
+    if (a.alpha_out) c.alpha_out += g;
+    launch_fwd_chunk<WT, OT, MODE, STATS, FAKE>(c, stream);
+  }
 }
 
 template <typename WT, typename OT, int MODE>

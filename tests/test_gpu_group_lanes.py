@@ -54,3 +54,28 @@ def test_modulate_and_pack(rows, cols, g):
     got = np.stack([(p >> (2 * i)) & 3 for i in range(4)], -1).reshape(rows, cols).astype(np.int8) - 1
     np.testing.assert_array_equal(got, codes.cpu().numpy())
     np.testing.assert_allclose(alpha.cpu().numpy(), fac[1] * al, rtol=4e-7)
+
+
+def test_more_octets_than_lanes_of_a_launch():
+    """Groups of 16, one octet per lane, in a weight of 2^35 and some elements:
+    more lanes than one launch may have."""
+    g, cols, tail = 16, 1 << 20, 3
+    rows = (1 << 15) + tail
+    need = rows * cols * (2 + 1 + 0.5)          # W, codes, statistics
+    if torch.cuda.mem_get_info()[0] < need * 1.1:
+        pytest.skip("needs 132 GB of free device memory")
+    W = torch.zeros((rows, cols), dtype=torch.bfloat16, device=DEV)
+    W[0] = torch.randn(cols, device=DEV).to(torch.bfloat16)
+    W[-tail:] = torch.randn((tail, cols), device=DEV).to(torch.bfloat16)
+    codes = torch.full((rows, cols), 7, dtype=torch.int8, device=DEV)
+    stats = torch.empty((rows * cols // g, 2), device=DEV)
+    one = [torch.tensor([v], device=DEV) for v in (0.0, 1.0, 1.0)]
+    p = catq.lmst_params(g, catq.HARD, strides=(0, 0, 0))
+    catq.catq_modulate_ternarize(W, *one, p, stats, 0, codes=codes)
+    for r in (0, rows - tail, rows - 1):
+        x = W[r].double().cpu().numpy().reshape(-1, g)
+        ref = lmst.modulate_ternarize(x, g, [0.0], [1.0], [1.0], lmst.HARD, strides=(0, 0, 0))["codes"]
+        np.testing.assert_array_equal(codes[r].cpu().numpy().reshape(ref.shape), ref)
+    assert not bool(codes[1:-tail].any())        # constant groups: all codes 0
+    del W, codes, stats
+    torch.cuda.empty_cache()
