@@ -1808,6 +1808,8 @@ catq_status gemm_run_epi(const GemmArgs& a, int a_t, int b_t, hipStream_t stream
   return CATQ_OK;
 }
 
+constexpr int64_t kFactorTiles = 112;
+
 catq_status gemm_run_factor(const GemmArgs& a, hipStream_t stream) {
   CATQ_REQUIRE(a.epi == 3 && (a.group_mode == 2 || (a.group_mode == 0 && a.batch == 1 &&
                                                      a.causal == 0)),
@@ -1835,9 +1837,14 @@ catq_status gemm_run_factor(const GemmArgs& a, hipStream_t stream) {
     // so the group numbering, stays the whole d_in)
     const int tm = (int)((a.M + 255) / 256), tn = (int)((a.N + 255) / 256);
     const int rem = (tm * tn) % 256;
-    // few tiles and a ragged token count: the product and the separate
-    // factor-gradient kernel
-    if (a.K % 64 != 0 && ((a.M + 127) / 128) * (a.N / 128) < 64) return CATQ_ERR_VALUE;
+    // too few 128 x 128 tiles to hide their epilogue (~10 us on a unit of its
+    // own): the product on 64 x 64 tiles and the separate factor-gradient kernel.
+    // Measured, two kernels / epilogue (us) at 64, 160, 512 and 1000 tokens: 16
+    // tiles 7.4 / 11.4, 7.9 / 12.3, 8.9 / 14.9, 10.8 / 18.8; 64 tiles 9.4 / 11.4, 9.9
+    // / 12.6, 11.1 / 15.1, 13.0 / 19.0; 96 tiles 10.9 / 11.5, 11.6 / 12.6, 13.4 / 15.2,
+    // 16.1 / 19.3; 144 tiles 13.2 / 11.5, 14.4 / 12.6, 17.3 / 15.4, 20.4 / 20.1; 256
+    // tiles 19.9 / 11.6, 21.3 / 12.7, 21.0 / 15.7, 22.8 / 21.0
+    if (((a.M + 127) / 128) * (a.N / 128) < kFactorTiles) return CATQ_ERR_VALUE;
     // fewer tiles than fill the chip: 128 x 128 (4096 x 2048 weights over 512
     // tokens: 36 us on 128 tiles of 256 x 256, 29 us on 512 of 128 x 128)
     if (tm * tn < kTiles256) {

@@ -210,8 +210,11 @@ def test_grouped_factor_epilogue(catq, mode, s_bwd, strides):
 
 
 
-@pytest.mark.parametrize("M,N,K,fused", [(1984, 512, 768, True),     # unsplit: epilogue
-                                         (1000, 512, 768, False),    # tokens % 64: two passes
+@pytest.mark.parametrize("M,N,K,fused", [(1984, 2048, 896, True),    # unsplit, 112 tiles of 128 x 128: epilogue
+                                         (1000, 2048, 896, True),    # the same with a ragged token count
+                                         (1984, 1896, 896, False),   # 105 tiles: two passes
+                                         (1984, 512, 768, False),    # few tiles: two passes
+                                         (1000, 512, 768, False),
                                          (8192, 256, 256, False)])   # split: two passes
 @pytest.mark.parametrize("mode,s_bwd,strides", [
     (lmst.SOFT, 30.0, (1, 1, 1)), (lmst.HARD, 30.0, (1, 1, 1)), (lmst.HARD, 0.0, (1, 1, 1)),

@@ -105,7 +105,7 @@ def test_nan_factor_with_finite_dy(catq, which, mode, s_bwd, dw):
     through a NaN dY, by the fused epilogue and by the separate kernel (dW_fake
     asked for), and no other group's."""
     import torch
-    N, K = (64, 256) if dw else (1024, 1024)    # 64 tiles of 128 x 128: the epilogue
+    N, K = (64, 256) if dw else (2048, 896)     # 112 tiles of 128 x 128: the epilogue
     W = to_dev_bf16(sg.normal_bf16(2, "W", (N, K), std=0.02))
     X, dY = (to_dev_bf16(sg.normal_bf16(2, k, s)) for k, s in (("X", (M, K)), ("Y", (M, N))))
     ng = N * K // G

@@ -1,8 +1,9 @@
-"""The transition function's two device forms (one exponential per weight
-while 2 cosh(2 s Delta) fits, the general one beyond) at sharpnesses on both
-sides of the line between them and on it, where the groups of one launch take
-both: fp32 fake weights and the factor gradients of the fp32 and the bf16
-(GEMM epilogue) paths against the oracle."""
+"""The transition function at sharpnesses from nearly linear to nearly hard: fp32
+fake weights, and the factor gradients of the fp32 and the bf16 (GEMM epilogue)
+paths against the oracle.  The backward has two device forms, one exponential per
+weight while 2 cosh(2 s Delta) is small enough and the general one beyond; the
+sharpnesses lie on both sides of the line between them and on it, where the
+groups of one launch take both."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,8 @@ from oracle import lmst
 pytestmark = pytest.mark.gpu
 
 N, K, M = 136, 256, 192
-SHARP = [0.01, 0.6, 30.0, 69.3, 75.0, 300.0]   # dz = 100 at s Delta = 34.66, Delta = 0.37 .. 0.67
+FUSED = (2048, 896)     # 112 tiles of 128 x 128: the factor epilogue
+SHARP = [0.01, 0.6, 30.0, 41.6, 69.3, 75.0, 300.0]   # dz = 60 at s Delta = 20.8, Delta = 0.37 .. 0.67
 
 
 @pytest.mark.parametrize("s", SHARP)
@@ -42,9 +44,10 @@ def test_soft_fp32(catq, s):
 
 @pytest.mark.parametrize("s", SHARP)
 @pytest.mark.parametrize("mode", [lmst.SOFT, lmst.HARD])
-def test_factor_gradients(catq, s, mode):
-    """bf16 (fused epilogue, 192 tokens) and the separate kernel on the
-    materialised G (dW_fake requested)."""
+@pytest.mark.parametrize("N,K", [(N, K), FUSED])
+def test_factor_gradients(catq, s, mode, N, K):
+    """bf16: the product with the separate kernel, or the fused epilogue, and the
+    separate kernel on the materialised G (dW_fake requested)."""
     import torch
     xb, dyb = sg.normal_bf16(43, "X", (M, K)), sg.normal_bf16(43, "Y", (M, N), std=1e-3)
     wb = sg.normal_bf16(43, "W", (N, K), std=0.02)
@@ -68,7 +71,8 @@ def test_factor_gradients(catq, s, mode):
             assert max_norm_err(host(a), b) <= 2e-5 + (4 * s + 1 / s ** 2) * 2.0 ** -22
 
 
-def test_constant_group_gradients(catq):
+@pytest.mark.parametrize("N,K", [(N, K), FUSED])
+def test_constant_group_gradients(catq, N, K):
     """alpha0 = 0: all gradients of the group are zero, none is NaN, fused and
     not."""
     import torch
@@ -147,7 +151,7 @@ def test_tiny_alpha_fused(catq, mode, s_bwd):
     """Groups of weights of 1e-31 and 1e-22 (2 s log2(e) / alpha beyond any bound
     on it that keeps constant groups finite) and groups with d_alpha <= 0, in the
     factor epilogue."""
-    n, k = 1024, 1024    # 64 tiles of 128 x 128
+    n, k = FUSED
     rng = sg.rng(48, "W")
     w = rng.standard_normal((n, k)) * 0.02
     for i, scale in enumerate((1e-31, 1e-22)):
@@ -176,7 +180,7 @@ def test_gradient_scale(catq, mode, s, dy_std, fused):
     """Small gradients keep their digits, with sharpnesses on both sides of the
     line between the two forms, and up to dz = 100, where a 2 sinh applied to the
     sum would lose them."""
-    n, k = (1024, 1024) if fused else (N, K)
+    n, k = FUSED if fused else (N, K)
     xb, dyb = sg.normal_bf16(49, "X", (M, k)), sg.normal_bf16(49, "Y", (M, n), std=dy_std)
     wb = sg.normal_bf16(49, "W", (n, k), std=0.02)
     ng = n * k // 128
