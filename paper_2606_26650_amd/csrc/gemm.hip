@@ -1633,6 +1633,17 @@ static void launch_bf16(GemmLaunch& L, hipStream_t stream) {
     // stages (copies two k tiles ahead; bit-identical; on the 235B-A22B-
     // shaped gate|up experts 1.17 -> 0.98 ms alone, 1.10 -> 1.09 ms in the
     // calibration step)
+    // Below 256 columns a 256-wide tile multiplies mostly padding: 128 x 128,
+    // four stages up to one tile per unit.  64 experts, 24000 rows, forward /
+    // input gradient of 128 columns: contraction 2048 44.6 -> 24.4 / 46.9 -> 24.0
+    // us, contraction 128 11.2 -> 6.9 / 10.9 -> 7.0
+    if (g.N < 256) {
+      if (((g.M + 127) / 128 + g.n_groups) * ((g.N + 127) / 128) <= 256)
+        launch_dma<128, 128, 2, 4, A_T == 1, B_T == 1, OutT, RT, 0, 4>(L, stream);
+      else
+        launch_dma<128, 128, 2, 2, A_T == 1, B_T == 1, OutT, RT>(L, stream);
+      return;
+    }
     if (A_T == 0 && B_T == 0)
       launch_dma<256, 256, 4, 4, false, false, OutT, RT, 0, 3>(L, stream);
     else
@@ -1640,6 +1651,10 @@ static void launch_bf16(GemmLaunch& L, hipStream_t stream) {
     return;
   }
   if (g.group_mode == 2 && dma_ok(L, A_T, B_T)) {
+    if (g.M < 256 || g.N < 256) {   // (as in gemm_run_factor)
+      launch_dma<128, 128, 2, 2, A_T == 1, B_T == 1, OutT, RT>(L, stream);
+      return;
+    }
     launch_dma<256, 256, 4, 4, A_T == 1, B_T == 1, OutT, RT>(L, stream);
     return;
   }
@@ -1885,7 +1900,14 @@ catq_status gemm_run_factor(const GemmArgs& a, hipStream_t stream) {
       }
     }
   }
-  launch_dma<256, 256, 4, 4, true, true, float, float, 3>(L, stream);
+  // experts with fewer than 256 rows or columns: most of a 256 x 256 tile and of
+  // its epilogue would be padding (64 experts, 24000 tokens: 128 x 128 weights
+  // 20.1 -> 13.3 us, 256 x 128 25.2 -> 13.5, 2048 x 128 62.8 -> 40.3; 512 x 512 stay,
+  // 36.0 against 38.1)
+  if (a.M < 256 || a.N < 256)
+    launch_dma<128, 128, 2, 2, true, true, float, float, 3>(L, stream);
+  else
+    launch_dma<256, 256, 4, 4, true, true, float, float, 3>(L, stream);
   CATQ_CHECK_LAUNCH("gemm factor epilogue");
   return CATQ_OK;
 }

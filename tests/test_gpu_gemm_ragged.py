@@ -88,6 +88,18 @@ def test_ragged_experts(catq, N, K):
         assert max_norm_err(a, b) <= 1e-3
 
 
+@pytest.mark.parametrize("N,K,rows", [(136, 256, 1), (248, 128, 1), (136, 128, 50)])
+def test_narrow_experts(catq, N, K, rows):
+    """Fewer than 256 columns, in the three products: 128 x 128 tiles, in four
+    stages, or (26000 rows, more than one tile per unit) in two."""
+    off = [rows * r for r in (0, 0, 70, 71, 400, 520)]
+    (y, dx, g), (Y, dX, G) = _case(catq, off[-1], N, K, E=5, off=off)
+    assert max_norm_err(y, Y) <= BF16
+    assert max_norm_err(dx, dX) <= BF16
+    for a, b in zip(g, G):
+        assert max_norm_err(a, b) <= 1e-3
+
+
 @pytest.mark.parametrize("M,N,K", [(130, 264, 256), (700, 4104, 2688)])
 def test_nan_row_stays_in_its_row(catq, M, N, K):
     """dY rows are the ragged contraction operand of dX: the last chunk of row
