@@ -1764,6 +1764,8 @@ catq_status gemm_run_split(const GemmArgs& a, int a_t, int b_t, catq_dtype in_dt
     CATQ_REQUIRE(((a_t && b_t) || a.K % 8 == 0) && (a_t || a.lda % 4 == 0) && (b_t || a.ldb % 4 == 0) &&
                      aligned16(a.A) && aligned16(a.B),
                  CATQ_ERR_SHAPE, "fp32 GEMM: contraction must be a multiple of 8, operands aligned");
+    CATQ_REQUIRE(!(a_t == 1 && b_t == 0), CATQ_ERR_VALUE,
+                 "fp32 GEMM: no kernel for a K-major A with a K-contiguous B");
     if (a_t == 0 && b_t == 0) launch_f32<0, 0>(L, stream);
     else if (a_t == 0 && b_t == 1) launch_f32<0, 1>(L, stream);
     else launch_f32<1, 1>(L, stream);

@@ -12,6 +12,7 @@
 #include <limits>
 
 #include "catq.h"
+#include "kernels.h"
 
 static int failures = 0;
 
@@ -223,6 +224,15 @@ int main() {
   EXPECT(catq_aux_moe_route(ff, 8, 4, 5, static_cast<int32_t*>(F), fw, static_cast<int32_t*>(F),
                             static_cast<int64_t*>(F), F, 4096, nullptr),
          CATQ_ERR_SHAPE);
+
+  // the fp32 product has no kernel for a K-major A with a K-contiguous B
+  {
+    catq::GemmArgs g = catq::gemm_args_default();
+    g.A = g.B = F;
+    g.C = F;
+    g.M = g.N = g.K = g.lda = g.ldb = g.ldc = 64;
+    EXPECT(catq::gemm_run_split(g, 1, 0, CATQ_F32, CATQ_F32, 1, 0, nullptr, CATQ_F32), CATQ_ERR_VALUE);
+  }
 
   // size helpers: degenerate and very large arguments must not overflow
   volatile size_t sink = 0;

@@ -40,7 +40,7 @@ def _build(tmp):
         objs = list(ex.map(compile_one, lib_build.SOURCES))
     drv = os.path.join(tmp, "abi_validation.o")
     cmd = [HIPCC, "-O1", "-g", "-std=c++17", "--offload-arch=gfx950", *SAN,
-           "-I", os.path.join(ROOT, "include"), "-c",
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c",
            os.path.join(ROOT, "tests", "sanitize", "abi_validation.cpp"), "-o", drv]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
