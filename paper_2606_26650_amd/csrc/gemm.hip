@@ -1125,19 +1125,18 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1)
 // small layers): what bounds them is the latency of each k tile on the few
 // compute units that work (0.7 us on 128 x 128 tiles, one k tile of copies in
 // flight, against 0.2 us of products).  So this kernel spreads the output
-// over BM x BN tiles of half that size on four waves and keeps S - 1 k tiles of
-// copies in flight.  A wave owns a quarter of the tile and contracts it in the
-// order of k, as the kernel above does: an element's bits do not depend on which
-// of the two a problem's size picks.  (The waves splitting each k tile instead,
-// partial tiles summed through LDS, halve the fragment reads: the three products
-// of 512 x 4096 x 2048 take 62.9 against 63.5 us.)
-// Operand tiles, their swizzles and the bounds of ragged extents are those of
-// the kernel above.
-template <int BM, int BN, int S, bool AKM, bool BKM, typename OutT>
+// over 64 x 64 tiles on four waves and keeps S - 1 k tiles of copies in flight.
+// A wave owns a quarter of the tile and contracts it in the order of k, as the
+// kernel above does: an element's bits do not depend on which of the two a
+// problem's size picks.  (The waves splitting each k tile instead, partial tiles
+// summed through LDS, halve the fragment reads: the three products of 512 x 4096
+// x 2048 take 62.9 against 63.5 us.)  Operand tiles, their swizzles and the bounds
+// of ragged extents are those of the kernel above.
+constexpr int kFewTile = 64;
+template <bool AKM, bool BKM, typename OutT>
 __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int NW = 4;
-  static_assert(BM == 64 && BN == 64, "four waves of 32 x 32");
+  constexpr int BM = kFewTile, BN = kFewTile, NW = 4, S = 4;   // four waves of 32 x 32
   using OA = std::conditional_t<AKM, DmaOpKM<BM, NW>, DmaOpNT<BM, NW, true>>;
   using OB = std::conditional_t<BKM, DmaOpKM<BN, NW>, DmaOpNT<BN, NW, true>>;
   constexpr int NI = OA::NI + OB::NI;              // copies per wave and k tile
@@ -1186,8 +1185,8 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
     const int behind = min(S - 2, nk - 1 - kt);
     if (behind == S - 2)
       wait_vmem_n<(S - 2) * NI>();
-    else if (S > 3 && behind == S - 3)
-      wait_vmem_n<(S > 3 ? S - 3 : 0) * NI>();
+    else if (behind == S - 3)
+      wait_vmem_n<(S - 3) * NI>();
     else
       wait_vmem();
     // every wave has also read its fragments of tile kt - 1, whose stage the
@@ -1537,23 +1536,23 @@ static void launch_dma(GemmLaunch& L, hipStream_t stream) {
                                    grid, block, 0, stream, L));
 }
 
-template <int BM, int BN, int S, int A_T, int B_T, typename OutT, typename RT>
+// (dense problems only: routed experts keep the larger tiles)
+template <int A_T, int B_T, typename OutT, typename RT>
 static void launch_few(GemmLaunch& L, hipStream_t stream) {
   const GemmArgs& g = L.g;
   L.group_m = 8;
   L.r_f32 = sizeof(RT) == 4;
-  // grouped rows: at most ceil(M/BM) + E m-tiles over all experts together
-  L.tiles_m = (int)((g.M + BM - 1) / BM) + (g.group_mode == 1 ? g.n_groups : 0);
-  L.tiles_n = (int)((g.N + BN - 1) / BN);
-  const dim3 grid((unsigned)(L.tiles_m * L.tiles_n * (g.group_mode == 2 ? g.n_groups : L.ksplit)));
+  L.tiles_m = (int)((g.M + kFewTile - 1) / kFewTile);
+  L.tiles_n = (int)((g.N + kFewTile - 1) / kFewTile);
+  const dim3 grid((unsigned)(L.tiles_m * L.tiles_n * L.ksplit));
   char tag[96];
-  trace_tag(tag, sizeof(tag), "gemm_few_kernel<%d, %d, %d, %s%s, %s>%s", BM, BN, S, A_T ? "k" : "n",
-                B_T ? "k" : "t", tname<OutT>(), g.group_mode ? ", experts" : "");
+  trace_tag(tag, sizeof(tag), "gemm_few_kernel<%s%s, %s>", A_T ? "k" : "n", B_T ? "k" : "t",
+            tname<OutT>());
   double flops, bytes;
   gemm_work(L, (int)sizeof(OutT), flops, bytes);
   CATQ_TRACED(stream, tag, flops, bytes, g.M, g.N, g.K,
-              hipLaunchKernelGGL((gemm_few_kernel<BM, BN, S, A_T == 1, B_T == 1, OutT>), grid,
-                                 dim3(256), 0, stream, L));
+              hipLaunchKernelGGL((gemm_few_kernel<A_T == 1, B_T == 1, OutT>), grid, dim3(256), 0,
+                                 stream, L));
 }
 
 // The direct-to-LDS kernel serves every unbatched bf16 problem whose row
@@ -1711,7 +1710,7 @@ static void launch_bf16(GemmLaunch& L, hipStream_t stream) {
     if constexpr (!(A_T == 1 && B_T == 0)) {
       auto tiles = [&](int64_t t) { return ((g.M + t - 1) / t) * ((g.N + t - 1) / t) * L.ksplit; };
       if (tiles(64) <= 512) {
-        launch_few<64, 64, 4, A_T, B_T, OutT, RT>(L, stream);
+        launch_few<A_T, B_T, OutT, RT>(L, stream);
         return;
       }
       if (tiles(128) <= 256) {
