@@ -389,6 +389,9 @@ catq_status catq_aux_swiglu_bwd(const void* gu, const void* da, int64_t rows, in
  *   inside each expert).  Requires k <= 16, E <= 1024.  NaN logits come after
  *   all others: whatever the logits hold, a token's k ids are valid and distinct
  *   and perm_row is a permutation; a selected NaN makes the token's weights NaN.
+ *   The workspace is part of the interface (checked, at least
+ *   catq_aux_moe_route_workspace_bytes); the kernels of this version leave it
+ *   unwritten.
  * catq_aux_moe_gather: xg[perm_row[t][j]] = x[t]          ([T*k][h])
  * catq_aux_moe_combine: y[t] = res[t] + sum_j w[t][j] * yg[perm_row[t][j]]
  *   (res and y of y_dtype, bf16 or fp32; res may be NULL)
