@@ -1266,9 +1266,9 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(GemmLaunch L) {
 // loop.  Within a group, lanes of half h hold k = 4h .. 4h + 3: a 16-byte load
 // of a K-contiguous row, four 4-byte loads (128-byte segments) of a K-major
 // one; product j contracts the pair k = j, 4 + j.
-// 1024 x 256 x 256: forward 35 -> 5.6 us, input gradient 37 -> 5.5 us, against a 64 x 64 LDS-tiled FMA kernel; 4096 x 1024
-// x 1024: 276 -> 116 us forward (74 TF/s).  Errors against float64 halve (the
-// sums are shorter).
+// Against a 64 x 64 LDS-tiled FMA kernel, 1024 x 256 x 256: forward 35 -> 5.6 us,
+// input gradient 37 -> 5.5 us; 4096 x 1024 x 1024: 276 -> 116 us forward (74 TF/s).
+// Errors against float64 halve (the sums are shorter).
 template <int A_T, int B_T, int F, int NW, int U>
 __global__ __launch_bounds__(NW * 64) void gemm_f32_kernel(GemmLaunch L) {
   constexpr int T = 32 * F;

@@ -147,10 +147,10 @@ __global__ __launch_bounds__(256) void lmst_fwd_kernel(FwdArgs a) {
 // bounds this pass is the vector ALU (float64 sums, two exponentials and one
 // reciprocal per weight), not HBM: 50M bf16 weights in groups of 128 take
 // statistics + soft 59 -> 40.7 us (5.1 TB/s) and the packed hard codes 29 ->
-// 21.0 us against four octets of different groups per lane.  A group of g weights is g / 32 adjacent
-// lanes, and load u of lane i of a group reads octet u * (g / 32) + i, so every
-// load instruction of a wave covers whole segments of 16 bytes per lane of a
-// group.
+// 21.0 us against four octets of different groups per lane.  A group of g weights
+// is g / 32 adjacent lanes, and load u of lane i of a group reads octet u * (g /
+// 32) + i, so every load instruction of a wave covers whole segments of 16 bytes
+// per lane of a group.
 template <typename WT, typename OT, int MODE, bool STATS, bool FAKE>
 __global__ __launch_bounds__(256) void lmst_group_kernel(FwdArgs a) {
   constexpr int OCT = 4;
