@@ -42,3 +42,25 @@ def test_rows_of_a_larger_product(catq, M, N, K, m, n, y_f32):
     assert torch.equal(dx, dX[:m])
     _, _, g = _products(catq, X, dY[:, :n].contiguous(), W[:n], y_f32)
     assert torch.equal(g, G[:n])
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 8), (5, 7, 72), (70, 333, 136),   # 64 x 64 tiles
+                                   (1500, 2049, 136),                       # 128 x 128 tiles in four stages
+                                   (3500, 2049, 136),                       # 128 x 128 tiles
+                                   (4100, 4099, 72)])                       # 256 x 256 tiles
+@pytest.mark.parametrize("y,r", [("bf16", None), ("bf16", "bf16"), ("f32", "bf16"), ("f32", "f32")])
+def test_odd_outputs(catq, M, N, K, y, r):
+    """Any number of outputs, in a buffer of no alignment beyond its start: rows
+    are stored element by element, and nothing past the last."""
+    import torch
+    dt = {"bf16": torch.bfloat16, "f32": torch.float32, None: None}
+    X, W = (to_dev_bf16(sg.normal_bf16(73, k, s)) for k, s in (("X", (M, K)), ("W", (N, K))))
+    R = None if r is None else to_dev_bf16(sg.normal_bf16(73, "Y", (M, N))).to(dt[r])
+    buf = torch.full((M * N + 64,), 7.0, dtype=dt[y], device="cuda")
+    catq.catq_fakeq_linear_fwd(X, W, buf[:M * N].view(M, N), M, N, K, residual=R)
+    torch.cuda.synchronize()
+    assert bool((buf[M * N:] == 7.0).all())
+    ref = X.float() @ W.float().T + (0 if R is None else R.float())
+    err = (buf[:M * N].view(M, N).float() - ref).abs().max() / ref.abs().max()
+    # one rounding to the output type, and two fp32 sums of K terms
+    assert err <= (2.0 ** -8 if y == "bf16" else 2e-6)

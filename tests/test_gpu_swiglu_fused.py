@@ -9,10 +9,10 @@ oracle.
   d[gate | up] bit for bit equal to the plain dX GEMM followed by the SwiGLU
   backward kernel, and sampled rows against the oracle's MLP backward on the
   stored values;
-* shapes the fused launch does not take (small, or F not a multiple of 256
-  for the backward) run the separate kernels inside the library; a ragged
-  token count and an F that is not a multiple of the 128 gate/up pairs of a
-  tile exercise the edge tiles;
+* shapes the fused launch does not take (small) run the separate kernels
+  inside the library; a ragged token count and an F that is no multiple of a
+  tile's columns (128 gate/up pairs, 256 of the backward) exercise the edge
+  tiles;
 * the 1.7B-shaped block's step with and without the fusion: same bits.
 
 Sampled-row bound for a: a = bf16(fp32 silu(g) * u) on the stored bf16 g, u,
@@ -96,7 +96,7 @@ def _down(catq, M, N, F, seed):
 @pytest.mark.parametrize("M,N,F", [(4096, 512, 4096),      # fused
                                    (4141, 256, 4096),      # fused, ragged M
                                    (2048, 256, 10240),     # fused, 1.25 rounds of tiles
-                                   (4096, 256, 4104),      # separate (F % 256)
+                                   (4096, 256, 4104),      # fused, partial column tile
                                    (512, 256, 384)])       # separate (small)
 def test_down_swiglu_bwd_fused(catq, M, N, F):
     import torch
