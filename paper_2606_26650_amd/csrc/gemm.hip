@@ -1903,9 +1903,12 @@ catq_status gemm_run_factor(const GemmArgs& a, hipStream_t stream) {
   }
   // experts with fewer than 256 rows or columns: most of a 256 x 256 tile and of
   // its epilogue would be padding (64 experts, 24000 tokens: 128 x 128 weights
-  // 20.1 -> 13.3 us, 256 x 128 25.2 -> 13.5, 2048 x 128 62.8 -> 40.3; 512 x 512 stay,
-  // 36.0 against 38.1)
-  if (a.M < 256 || a.N < 256)
+  // 20.1 -> 13.3 us, 256 x 128 25.2 -> 13.5, 2048 x 128 62.8 -> 40.3); and fewer tiles
+  // than fill the chip, as above (8 experts of 512 x 2048, 128 tiles, 4096 tokens
+  // 31.4 -> 23.0, 64 of 256 x 512, 128 tiles, 21.9 -> 14.7; 64 of 512 x 512, 256 tiles,
+  // stay: 24.7 against 28.0)
+  if (a.M < 256 || a.N < 256 ||
+      a.n_groups * ((a.M + 255) / 256) * ((a.N + 255) / 256) < kTiles256)
     launch_dma<128, 128, 2, 2, true, true, float, float, 3>(L, stream);
   else
     launch_dma<256, 256, 4, 4, true, true, float, float, 3>(L, stream);

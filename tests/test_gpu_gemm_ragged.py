@@ -78,7 +78,8 @@ def test_ragged_dense(catq, M, N, K, mode):
         assert max_norm_err(a, b) <= 1e-3
 
 
-@pytest.mark.parametrize("N,K", [(264, 384), (1032, 128)])
+@pytest.mark.parametrize("N,K", [(264, 384), (1032, 128),
+                                 (1032, 1664)])   # 175 tiles of 256 x 256: the larger factor tiles
 def test_ragged_experts(catq, N, K):
     off = [0, 0, 70, 71, 400, 520]   # an empty expert, one row, remainders
     (y, dx, g), (Y, dX, G) = _case(catq, 520, N, K, E=5, off=off)
